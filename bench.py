@@ -58,7 +58,8 @@ def kernel_name(kernel: str, kind: int, D: int, shape: int, b: int, split: bool 
     return (f"k_tile_numeric<{T}, {D}, {sp}, {tq}, {tf(bf)}, {tf(kind == 3)}, {tf(full_k)}, "
             f"{ws}>")
 
-KERNEL_SOURCES = ("paper_2009_03551_amd/csrc/tc2_tile.hip", "paper_2009_03551_amd/csrc/tc2_device.h",
+KERNEL_SOURCES = ("paper_2009_03551_amd/csrc/tc2_tile.hip",
+                  "paper_2009_03551_amd/csrc/tc2_tile_numeric.h", "paper_2009_03551_amd/csrc/tc2_device.h",
                   "paper_2009_03551_amd/csrc/tc2_internal.h", "paper_2009_03551_amd/csrc/tc2_kernels.hip")
 
 

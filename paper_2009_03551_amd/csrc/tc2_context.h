@@ -231,7 +231,7 @@ struct tc2_ctx {
   int cur_prec = tc2::P_FP64;
   bool have_iterate = false;      // a solve has produced (or begun) an iterate
   // work buffers
-  tc2::DBuf cand_cnt, cand_rp, cand_ci, item_cnt, item_rp, item_row, item_c0, partial;
+  tc2::DBuf cand_cnt, cand_rp, cand_ci, item_cnt, item_rp, item_row, item_c0, partial, sum_rows;
   tc2::DBuf stage, kept_ij, counters, exec_pairs, rowcnt, cursor, tmp_ci, tmp_src, new_src;
   tc2::HostPin pin_graph;         // per-update readback of the graph path
   tc2::HostPin pin_loop;          // active / branch flags in, bad / nominal out
@@ -280,6 +280,7 @@ struct tc2_ctx {
   // test knobs (environment, read at setup): shorter panel passes in the
   // tiled kernel, and a tiny stage that overflows every update
   int test_kl_chunk = 0;
+  int test_fine_subs = tc2::FINE_SUBS;  // fewer: sub-tiles not split into parts
   long long test_stage_cap = 0;
   int test_no_zero_skip = 0;      // issue every product (masks not passed to the kernel)
   int test_waves_per_column = 0;  // 1: one wave per sub-tile column in every numeric kernel

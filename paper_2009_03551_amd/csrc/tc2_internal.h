@@ -169,7 +169,8 @@ struct TileArgs {
   unsigned long long* log_count;
   long long log_cap;      // 0: no logging
   int kl_chunk;           // 0: default panel pass length
-  int ksteps;
+  int b;                  // block size
+  int ksteps;             // ceil(b / 4): K-steps of 4 in the padded tile
   int waves_per_column;   // 1: one wave per column of the 4 x 4 sub-tile (tests compare)
   int n_tiles;
   const int* rp;
@@ -197,6 +198,8 @@ struct TileArgs {
   int* overflow;
   int* bad;
   double* partial;        // n_tiles x NQ
+  double* rows;           // trace sums per output, of an update in parts (tile_rows_bytes)
+  int fine_subs;          // most sub-tiles of an update in parts (at most FINE_SUBS)
   unsigned long long* exec_pairs;  // block products issued
 };
 
@@ -262,7 +265,20 @@ void launch_tiles(hipStream_t st, int pass, const PanelArgs& a);
 bool launch_tile_numeric(hipStream_t st, int prec, const TileArgs& a);  // false: no such shape
 bool tile_shape_available(int kind, int D, int shape);
 int tile_shape_default(int kind, int D);
-int tile_subs(int shape);  // workgroups per tile of 8 x 8 output blocks
+int tile_subs(int shape);  // sub-tiles per tile of 8 x 8 output blocks
+// Updates of at most this many sub-tiles run in parts of 8 outputs (one per
+// wave), others a sub-tile per workgroup.  512 workgroups fit on the chip: with
+// few sub-tiles the parts fill compute units that would idle or wait for the
+// longest sub-tile (64-atom chain, 72 sub-tiles: 183 -> 70 us per update;
+// 1024-atom chain: 723 -> 520; 100 atoms in three directions, 364: 723 -> 633),
+// with many, operands shared by fewer outputs cost more than the balance gives
+// (343 atoms, 3784 sub-tiles: 5 % slower in parts).
+constexpr int FINE_SUBS = 1024;
+// bytes of the trace sums per output of those parts
+inline size_t tile_rows_bytes(long long n_tiles) {
+  const long long n = n_tiles < 1 ? 1 : n_tiles;
+  return (size_t)(n < FINE_SUBS ? n : FINE_SUBS) * CS * CS * NQ * 8;
+}
 const char* tile_shape_name(int shape);
 void launch_copy_through(hipStream_t st, int prec, const CopyArgs& a, int nnz);
 // nnz_dev (optional): the entry count on the device, at most nnz (the grid)

@@ -342,6 +342,8 @@ static tc2_status setup_impl(const tc2_problem* probs, int32_t np, const tc2_opt
   for (int k = 0; k < 4; ++k) ctx->shape[k] = tile_shape_default(k, D);
   if (ctx->tune) tune_load(ctx);
   if (const char* v = getenv("TC2_TEST_KL_CHUNK")) ctx->test_kl_chunk = std::max(0, atoi(v));
+  if (const char* v = getenv("TC2_TEST_FINE_SUBS"))
+    ctx->test_fine_subs = std::min(std::max(0, atoi(v)), FINE_SUBS);
   if (const char* v = getenv("TC2_TEST_STAGE_CAP")) ctx->test_stage_cap = std::max(0LL, atoll(v));
   if (const char* v = getenv("TC2_TEST_NO_ZERO_SKIP")) ctx->test_no_zero_skip = atoi(v) != 0;
   if (const char* v = getenv("TC2_TEST_WAVES_PER_COLUMN")) ctx->test_waves_per_column = atoi(v);
@@ -755,6 +757,7 @@ tc2_status step(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
   }
   // room for the partial sums of any sub-tile shape (at most 4 per tile)
   HIPCHK(ctx->partial.reserve((size_t)std::max((long long)n_work * (tiled ? 4 : 1), (long long)nb) * NQ * 8));
+  if (tiled) HIPCHK(ctx->sum_rows.reserve(tile_rows_bytes(n_work)));
   if (ctx->profile) HIPCHK(hipEventRecord(ctx->pev[1], st));
 
   // ---- numeric (retried with a larger stage if it overflows).  The stage
@@ -789,6 +792,7 @@ tc2_status step(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
   auto tile_args = [&](int cap, int shape) {
     TileArgs ta{};
     ta.D = D;
+    ta.b = ctx->b;
     ta.ksteps = (ctx->b + 3) / 4;
     ta.n_tiles = n_work;
     ta.rp = ctx->rp[c].as<int>();
@@ -820,6 +824,8 @@ tc2_status step(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
     ta.overflow = cnt + 2;
     ta.bad = ctx->bad.as<int>();
     ta.partial = ctx->partial.as<double>();
+    ta.rows = ctx->sum_rows.as<double>();
+    ta.fine_subs = ctx->test_fine_subs;
     ta.exec_pairs = ctx->exec_pairs.as<unsigned long long>();
     ta.bf16 = (ctx->op_bf16 && ctx->cur_prec == P_FP32) ? 1 : 0;
     ta.wide = wide_now;
@@ -1181,6 +1187,7 @@ int step_graph(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
     GRESERVE(ctx->tile_p.reserve((size_t)std::max<long long>(ctx->tile_bound, 1) * 4));
     GRESERVE(ctx->tile_q.reserve((size_t)std::max<long long>(ctx->tile_bound, 1) * 4));
     GRESERVE(ctx->partial.reserve((size_t)std::max(ctx->tile_bound * 4, (long long)nb) * NQ * 8));
+    GRESERVE(ctx->sum_rows.reserve(tile_rows_bytes(ctx->tile_bound)));
     GRESERVE(ctx->sys_lo.reserve((size_t)ctx->nsys * 4));
     GRESERVE(ctx->sys_hi.reserve((size_t)ctx->nsys * 4));
     GRESERVE(ctx->stage.reserve((size_t)cap * tile));
@@ -1230,7 +1237,7 @@ int step_graph(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
         (uintptr_t)ctx->sys_hi.p, (uintptr_t)ctx->panel_cnt.p, (uintptr_t)ctx->panel_rp.p,
         (uintptr_t)ctx->tile_cnt.p, (uintptr_t)ctx->tile_rp.p, (uintptr_t)ctx->tile_pairs.p,
         (uintptr_t)ctx->tile_bits.p, (uintptr_t)ctx->nominal.p, (uintptr_t)ctx->mask[c].p,
-        (uintptr_t)ctx->mask[n].p};
+        (uintptr_t)ctx->mask[n].p, (uintptr_t)ctx->sum_rows.p};
     // the three parts of the update, as stream work (captured or not)
     auto rec_pre = [&]() {
       (void)count_nominal(ctx, st, ctx->rp[c].as<int>());
@@ -1279,6 +1286,7 @@ int step_graph(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
     auto rec_num = [&]() -> bool {
       TileArgs ta{};
       ta.D = D;
+      ta.b = ctx->b;
       ta.ksteps = (ctx->b + 3) / 4;
       ta.n_tiles = (int)std::min<long long>(ctx->tile_bound, INT32_MAX / 4);
       ta.n_tiles_dev = ctx->tile_rp.as<int>() + nc;
@@ -1310,6 +1318,8 @@ int step_graph(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
       ta.overflow = cnt + 2;
       ta.bad = ctx->bad.as<int>();
       ta.partial = ctx->partial.as<double>();
+      ta.rows = ctx->sum_rows.as<double>();
+      ta.fine_subs = ctx->test_fine_subs;
       ta.exec_pairs = ctx->exec_pairs.as<unsigned long long>();
       ta.bf16 = (ctx->op_bf16 && ctx->cur_prec == P_FP32) ? 1 : 0;
       ta.wide = kind == K_WIDE ? 1 : 0;

@@ -1,0 +1,6 @@
+// The tiled numeric kernel: FP64 values, 2 directions.
+#include "tc2_tile_numeric.h"
+
+namespace tc2 {
+template bool tile_launch<double, 2>(hipStream_t, const TileArgs&);
+}  // namespace tc2

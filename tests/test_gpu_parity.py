@@ -315,3 +315,38 @@ def test_more_waves_per_column_equal_one(knob, case):
         assert np.array_equal(x.val, y.val)
     for p, q in zip(a.alpha, b.alpha):
         assert p == pytest.approx(q, rel=1e-12)
+
+
+@pytest.mark.parametrize("case", [
+    dict(name="chain64", kw=dict(n=37, b=5, occ=2, eps=1e-6, seed=17), fine=0),
+    dict(name="chain64", kw=dict(n=70, b=3, occ=1, eps=1e-6, seed=23), fine=0),
+    dict(name="chain64", kw=dict(n=29, b=12, occ=5, eps=1e-6, seed=23), fine=0),
+    dict(name="cube10", kw=dict(L=4, n_dir=0), fine=0),
+    dict(name="cube10", kw=dict(L=5, n_dir=2, eps=1e-5), fine=0, chunk=64),
+    # columns of 32 blocks of 16 x 16, more than half the ring
+    dict(name="cube20", kw=dict(L=4, b=16, occ=6, eps=1e-6), fine=0),
+    # both splits within one solve (the choice is made on the device)
+    dict(name="cube10", kw=dict(L=5, n_dir=3, eps=1e-5), fine=300,
+         variant=dict(skip="bound", graph=True)),
+    dict(name="cube10", kw=dict(L=5, n_dir=3, eps=1e-5), fine=0,
+         variant=dict(precision="fp32", wide=True, fp64_first=2, closing_fp64=2, skip="bound",
+                      graph=True)),
+    dict(name="cube10", kw=dict(L=4, eps=1e-5), fine=0,
+         variant=dict(precision="bf16", wide=True, fp64_first=2, closing_fp64=2, skip="bound")),
+])
+def test_parts_of_a_subtile_equal_the_subtile(knob, case):
+    # a sub-tile computed in parts of eight outputs by several workgroups sums
+    # the same products, and then the same traces, in the same order as one
+    # workgroup: the results are bitwise identical
+    if "chunk" in case:
+        knob("TC2_TEST_KL_CHUNK", case["chunk"])
+    s = W.config_system(case["name"], **case["kw"])
+    variant = case.get("variant", {})
+    a = T.solve(s, **variant)[0]
+    knob("TC2_TEST_FINE_SUBS", case["fine"])
+    b = T.solve(s, **variant)[0]
+    print(f"  {case['name']} {case['kw']}: {a.iters} updates {a.branches}", flush=True)
+    assert a.branches == b.branches and a.iters == b.iters and a.alpha == b.alpha
+    for x, y in zip([a.X0] + a.X1, [b.X0] + b.X1):
+        assert np.array_equal(x.row_ptr, y.row_ptr) and np.array_equal(x.col, y.col)
+        assert np.array_equal(x.val, y.val)
