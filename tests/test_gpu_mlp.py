@@ -63,3 +63,38 @@ def test_rejects_bad_input():
     X[0, 0] = np.nan
     with pytest.raises(T.TC2Error):
         T.mlp_grad(theta, X, y)
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 255, 257, 4097])
+def test_gradient_at_the_edges_of_its_tiles(n):
+    # 16 samples per matrix product, 256 per workgroup; FP32 sums of at most
+    # 64 units and 256 samples: below 320 * 2^-24 = 2e-5 of the largest entry
+    # without cancellation, 1e-4 with it as above
+    theta, X, y = problem(n=n, seed=n)
+    g, loss = T.mlp_grad(theta, X, y)
+    lr, gr = M.loss_and_grad(theta.astype(np.float64), X.astype(np.float64), y.astype(np.float64))
+    err = np.abs(g - gr).max() / np.abs(gr).max()
+    print(f"  n={n}: loss error {abs(loss - lr) / abs(lr):.2e}, grad error {err:.2e}", flush=True)
+    assert abs(loss - lr) < 1e-5 * abs(lr)
+    assert err < 1e-4
+
+
+def test_activation_beyond_fp32_that_reaches_no_output_adds_nothing():
+    # sample 5 overflows unit 0 of layer 1, which closes every unit of layer 2:
+    # its gradient is that of b3 alone
+    theta, X, y = problem(n=40, seed=8)
+    theta[0] = 10.0                       # W1[0][0]
+    theta[576:4672:64] = -1.0             # W2[:, 0]
+    X[5, 0] = 3e38
+    g, loss = T.mlp_grad(theta, X, y)
+    lr, gr = M.loss_and_grad(theta.astype(np.float64), X.astype(np.float64), y.astype(np.float64))
+    assert np.isfinite(g).all() and abs(loss - lr) < 1e-5 * abs(lr)
+    assert np.abs(g - gr).max() / np.abs(gr).max() < 1e-4
+
+
+@pytest.mark.parametrize("where", ["theta", "x", "y"])
+def test_gradient_refuses_a_value_that_is_not_finite(where):
+    theta, X, y = problem(n=300, seed=4)
+    {"theta": theta, "x": X.reshape(-1), "y": y}[where][-1] = np.nan if where == "y" else np.inf
+    with pytest.raises(T.TC2Error):
+        T.mlp_grad(theta, X, y)
