@@ -8,6 +8,10 @@
 #include "tc2_internal.h"
 #include "../../include/tc2.h"
 
+#include <stdlib.h>
+#include <sys/mman.h>
+
+#include <algorithm>
 #include <string>
 #include <utility>
 #include <vector>
@@ -17,12 +21,12 @@ namespace tc2 {
 // ------------------------------------------------------------------ device buffers
 // Buffers of at least VM_MIN bytes live in a reserved virtual range with
 // physical chunks mapped as they grow, taken from and given back to a pool
-// per device (tc2_memory.hip); smaller ones are plain allocations.
+// per device (tc2_memory.hip); smaller ones are plain allocations, kept there
+// for reuse as well.
 struct DBuf;
 constexpr size_t VM_MIN = (size_t)64 << 20;
 hipError_t vm_grow(DBuf& b, size_t n);     // map up to >= n bytes, contents kept
 void vm_release(DBuf& b);                  // chunks back to the pool, range freed
-hipError_t dev_malloc(void** p, size_t n); // hipMalloc, retried after pool_trim
 void pool_trim();                          // pooled chunks of the device to the GPU driver
 
 struct DBuf {
@@ -41,7 +45,7 @@ struct DBuf {
       vm_release(*this);
       return;
     }
-    if (p) (void)hipFree(p);
+    dev_free(p);
     p = nullptr;
     cap = 0;
   }
@@ -105,7 +109,7 @@ struct DBuf {
       e = hipMemcpyAsync(q, p, keep < cap ? keep : cap, hipMemcpyDeviceToDevice, st);
       if (e == hipSuccess) e = hipStreamSynchronize(st);
       if (e != hipSuccess) {
-        (void)hipFree(q);
+        dev_free(q);
         return e;
       }
     }
@@ -151,10 +155,36 @@ struct HostPin {
   }
 };
 
+// A host array that is not cleared and keeps its memory while it suffices; large
+// ones ask for huge pages (first touch of 4 KiB pages takes as long as the copy).
+struct HostArray {
+  double* p = nullptr;
+  size_t cap = 0;
+  HostArray() = default;
+  HostArray(const HostArray&) = delete;
+  HostArray& operator=(const HostArray&) = delete;
+  HostArray(HostArray&& o) noexcept : p(o.p), cap(o.cap) { o.p = nullptr, o.cap = 0; }
+  ~HostArray() { free(p); }
+  bool resize(size_t n) {
+    if (n <= cap && p) return true;
+    free(p);
+    constexpr size_t PAGE = (size_t)2 << 20;
+    const size_t bytes = std::max<size_t>(n, 1) * sizeof(double);
+    if (bytes >= 2 * PAGE) {
+      p = (double*)aligned_alloc(PAGE, (bytes + PAGE - 1) / PAGE * PAGE);
+      if (p) (void)madvise(p, bytes, MADV_HUGEPAGE);
+    } else {
+      p = (double*)malloc(bytes);
+    }
+    cap = p ? n : 0;
+    return p != nullptr;
+  }
+};
+
 struct HostBsr {
   std::vector<int64_t> row_ptr;
   std::vector<int32_t> col;
-  std::vector<double> val;
+  HostArray val;
 };
 
 struct SysInfo {

@@ -102,7 +102,7 @@ unsigned grid_for(long long n) {
 struct Dev {  // device allocation released with its owner
   void* p = nullptr;
   ~Dev() {
-    if (p) (void)hipFree(p);
+    tc2::dev_free(p);
   }
   hipError_t alloc(size_t bytes) { return tc2::dev_malloc(&p, bytes ? bytes : 8); }
   double* d() const { return (double*)p; }

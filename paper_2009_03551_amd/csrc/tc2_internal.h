@@ -15,6 +15,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <map>
+#include <vector>
+
 namespace tc2 {
 
 constexpr int BP = 16;        // padded block dimension
@@ -243,6 +246,26 @@ struct CompactArgs {
 // hipMalloc that, when the device is out of memory, first returns the chunks
 // the solver keeps pooled for reuse to the driver and tries again
 hipError_t dev_malloc(void** p, size_t n);
+void dev_free(void* p);  // as hipFree: waits for the device (see MemScope)
+
+// Buffers of this thread that dev_free releases while a scope is open are not
+// waited for one by one.  open: they serve this thread's later dev_mallocs,
+// whose uses follow on the same stream, and the wait is at the scope's end.
+// open_idle: the device is idle, and nothing is launched in the scope.
+typedef std::map<size_t, std::vector<void*>> SizeLists;
+struct MemScope {
+  SizeLists free;
+  hipStream_t st = nullptr;
+  int dev = 0;
+  bool is_open = false, idle = false;
+  MemScope* outer = nullptr;
+  MemScope() = default;
+  MemScope(const MemScope&) = delete;
+  MemScope& operator=(const MemScope&) = delete;
+  ~MemScope();
+  void open(hipStream_t s);
+  void open_idle();
+};
 
 // kernels (launch wrappers), all asynchronous on `st`
 void launch_gershgorin(hipStream_t st, int nb, int b, const int* rp, const int* ci,

@@ -240,7 +240,7 @@ unsigned grid_for(long long n, int per_block = 256) {
 struct Buf {  // device allocation released with its owner
   void* p = nullptr;
   ~Buf() {
-    if (p) (void)hipFree(p);
+    tc2::dev_free(p);
   }
   Buf() = default;
   Buf(const Buf&) = delete;
@@ -248,14 +248,14 @@ struct Buf {  // device allocation released with its owner
   Buf(Buf&& o) noexcept : p(o.p) { o.p = nullptr; }
   Buf& operator=(Buf&& o) noexcept {
     if (this != &o) {
-      if (p) (void)hipFree(p);
+      tc2::dev_free(p);
       p = o.p;
       o.p = nullptr;
     }
     return *this;
   }
   hipError_t alloc(size_t bytes) {
-    if (p) (void)hipFree(p);
+    tc2::dev_free(p);
     p = nullptr;
     return tc2::dev_malloc(&p, bytes ? bytes : 8);
   }
@@ -274,12 +274,15 @@ struct GMat {
 
 struct Ctx {
   hipStream_t st = nullptr;
-  hipStream_t own = nullptr;
+  struct Own {
+    hipStream_t s = nullptr;
+    ~Own() {
+      if (s) (void)hipStreamDestroy(s);
+    }
+  } own;
+  tc2::MemScope scope;  // all work of a call is on st: ends after the buffers, before the stream
   Buf part, cnt, keep, src;
   std::vector<int> hcnt;
-  ~Ctx() {
-    if (own) (void)hipStreamDestroy(own);
-  }
 };
 
 tc2_status upload_pattern(GMat& m, hipStream_t st) {
@@ -544,9 +547,10 @@ tc2_status start(const tc2_lowdin_options* o, Ctx& x) {
   if (tc2_status s = select_gfx950(o->device, nullptr); s != TC2_OK) return s;
   x.st = (hipStream_t)o->hip_stream;
   if (!x.st) {
-    LCHK(hipStreamCreateWithFlags(&x.own, hipStreamNonBlocking));
-    x.st = x.own;
+    LCHK(hipStreamCreateWithFlags(&x.own.s, hipStreamNonBlocking));
+    x.st = x.own.s;
   }
+  x.scope.open(x.st);
   return TC2_OK;
 }
 

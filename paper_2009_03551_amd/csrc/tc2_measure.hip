@@ -283,7 +283,7 @@ __global__ void k_compare_missing(long long nnz, int D, int m, const T* __restri
 struct Tmp {
   void* p = nullptr;
   ~Tmp() {
-    if (p) (void)hipFree(p);
+    tc2::dev_free(p);
   }
   hipError_t alloc(size_t n) { return tc2::dev_malloc(&p, n < 256 ? 256 : n); }
   template <typename T> T* as() const { return (T*)p; }

@@ -383,7 +383,7 @@ namespace {
 struct DevMem {
   void* p = nullptr;
   ~DevMem() {
-    if (p) (void)hipFree(p);
+    tc2::dev_free(p);
   }
   hipError_t alloc(size_t n) { return tc2::dev_malloc(&p, n < 256 ? 256 : n); }
   template <typename T> T* as() const { return (T*)p; }

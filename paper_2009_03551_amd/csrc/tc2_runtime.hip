@@ -162,7 +162,6 @@ const char* tc2_strerror(tc2_status s) {
 void tc2_free(tc2_ctx* ctx) {
   if (!ctx) return;
   (void)hipSetDevice(ctx->device);
-  const int dev = ctx->device;
   if (ctx->own) (void)hipStreamDestroy(ctx->own);
   for (hipEvent_t& e : ctx->pev)
     if (e) (void)hipEventDestroy(e);
@@ -172,8 +171,9 @@ void tc2_free(tc2_ctx* ctx) {
     if (g) (void)hipGraphExecDestroy(g);
   if (ctx->run.ev0) (void)hipEventDestroy(ctx->run.ev0);
   if (ctx->run.ev1) (void)hipEventDestroy(ctx->run.ev1);
+  tc2::MemScope scope;
+  scope.open_idle();
   delete ctx;
-  (void)dev;
 }
 
 tc2_status tc2_trim_memory(int32_t device) {
@@ -1535,28 +1535,28 @@ tc2_status export_results(tc2_ctx* ctx, hipStream_t st) {
   HIPCHK(hipMemcpyAsync(rp.data(), ctx->rp[c].p, (size_t)(nb + 1) * 4, hipMemcpyDeviceToHost, st));
   HIPCHK(hipMemcpyAsync(ci.data(), ctx->ci[c].p, (size_t)nnz * 4, hipMemcpyDeviceToHost, st));
   HIPCHK(ctx->xfer.reserve((size_t)std::max(nnz, 1) * b * b * 8));
-  std::vector<double> v((size_t)nnz * b * b);
-  ctx->out_x0.assign(ctx->nsys, HostBsr());
-  for (int d = 0; d < MAXD; ++d) ctx->out_x1[d].assign(d < D ? ctx->nsys : 0, HostBsr());
+  HIPCHK(hipStreamSynchronize(st));
+  // the arrays of an earlier run are written again
+  ctx->out_x0.resize(ctx->nsys);
+  for (int d = 0; d < MAXD; ++d) ctx->out_x1[d].resize(d < D ? ctx->nsys : 0);
+  const size_t bb = (size_t)b * b;
   for (int m = 0; m <= D; ++m) {
     launch_export(st, ctx->cur_prec, nnz, D, m, b, ctx->xv[c].p, ctx->xfer.as<double>());
-    HIPCHK(hipMemcpyAsync(v.data(), ctx->xfer.p, v.size() * 8, hipMemcpyDeviceToHost, st));
-    HIPCHK(hipStreamSynchronize(st));
+    // the blocks of a system are contiguous: copied to where they stay
     for (int s = 0; s < ctx->nsys; ++s) {
       const SysInfo& si = ctx->sys[s];
       HostBsr& hb = (m == 0) ? ctx->out_x0[s] : ctx->out_x1[m - 1][s];
-      hb.row_ptr.assign(1, 0);
-      hb.col.clear();
-      hb.val.clear();
-      for (int i = 0; i < si.nb; ++i) {
-        int I = si.row0 + i;
-        for (int p = rp[I]; p < rp[I + 1]; ++p) {
-          hb.col.push_back(ci[p] - si.row0);
-          hb.val.insert(hb.val.end(), v.begin() + (size_t)p * b * b, v.begin() + (size_t)(p + 1) * b * b);
-        }
-        hb.row_ptr.push_back((int64_t)hb.col.size());
-      }
+      const int p0 = rp[si.row0], n = rp[si.row0 + si.nb] - p0;
+      if (!hb.val.resize((size_t)n * bb)) return TC2_ENOMEM;
+      if (n)
+        HIPCHK(hipMemcpyAsync(hb.val.p, ctx->xfer.as<double>() + (size_t)p0 * bb, (size_t)n * bb * 8,
+                              hipMemcpyDeviceToHost, st));
+      hb.row_ptr.resize((size_t)si.nb + 1);
+      for (int i = 0; i <= si.nb; ++i) hb.row_ptr[i] = rp[si.row0 + i] - p0;
+      hb.col.resize((size_t)n);
+      for (int p = 0; p < n; ++p) hb.col[p] = ci[p0 + p] - si.row0;
     }
+    HIPCHK(hipStreamSynchronize(st));  // the staging buffer is free again
   }
   return TC2_OK;
 }
@@ -1967,10 +1967,10 @@ tc2_status finish_solve(tc2_ctx* ctx, tc2_result* res) {
     Rs.kept_blocks = final_rp[ctx->sys[s].row0 + ctx->sys[s].nb] - final_rp[ctx->sys[s].row0];
     if (ctx->export_m) {
       HostBsr& x0 = ctx->out_x0[s];
-      Rs.X0 = tc2_bsr{ctx->sys[s].nb, b, x0.row_ptr.data(), x0.col.data(), x0.val.data()};
+      Rs.X0 = tc2_bsr{ctx->sys[s].nb, b, x0.row_ptr.data(), x0.col.data(), x0.val.p};
       for (int d = 0; d < D; ++d) {
         HostBsr& x1 = ctx->out_x1[d][s];
-        Rs.X1[d] = tc2_bsr{ctx->sys[s].nb, b, x1.row_ptr.data(), x1.col.data(), x1.val.data()};
+        Rs.X1[d] = tc2_bsr{ctx->sys[s].nb, b, x1.row_ptr.data(), x1.col.data(), x1.val.p};
       }
     }
     if (Rs.status < 0 && (worst >= 0 || Rs.status < worst)) worst = Rs.status;

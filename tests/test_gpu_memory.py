@@ -1,0 +1,38 @@
+"""Device buffers kept for reuse: solves of several threads at once, with
+released buffers passing between them, equal the same solves one by one."""
+import threading
+
+import numpy as np
+import pytest
+
+from paper_2009_03551_amd import tc2 as T
+from paper_2009_03551_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def matrices(r):
+    return [a for m in [r.X0] + r.X1 for a in (m.row_ptr, m.col, m.val)]
+
+
+@pytest.mark.parametrize("variant", [dict(), dict(precision="fp32", wide=True, fp64_first=2, closing_fp64=2)])
+def test_threads_share_released_buffers(variant):
+    systems = [W.config_system("chain64", n=29 + 8 * k, b=5 + k, occ=2, eps=1e-6, seed=k) for k in range(4)]
+    alone = [matrices(T.solve(s, **variant)[0]) for s in systems]
+    out = [[] for _ in systems]
+
+    def work(k):
+        for _ in range(5):
+            out[k].append(matrices(T.solve(systems[k], **variant)[0]))
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(len(systems))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    T.trim_memory(0)  # the kept buffers go back; the next solve starts from none
+    for k, s in enumerate(systems):
+        out[k].append(matrices(T.solve(s, **variant)[0]))
+        assert len(out[k]) == 6
+        for got in out[k]:
+            assert all(np.array_equal(a, b) for a, b in zip(got, alone[k]))
