@@ -125,7 +125,14 @@ struct EpiCtx {
   int stage_cap;
   int* overflow;
   int* bad;
+  int* rowcnt;
 };
+
+// a kept upper block (I, J) and its mirror image in the new row lengths
+__device__ __forceinline__ void count_kept(int* rowcnt, int I, int J) {
+  atomicAdd(&rowcnt[I], 1);
+  if (J != I) atomicAdd(&rowcnt[J], 1);
+}
 
 // Epilogue of one output block C_IJ (accumulators of X0*X0 and of
 // X0*X1_d + X1_d*X0) for the TC2 update (Sec. 2.2): combine with the branch
@@ -188,7 +195,10 @@ __device__ __forceinline__ bool epilogue(const EpiCtx& E, const A* acc, int I, i
           const int r = A::row(lane, j);
           st[m * BS + (tr ? col * BP + r : r * BP + col)] = keep[m] ? (T)v[m][j] : (T)0;
         }
-      if (lane == 0) E.kept_ij[slot] = tr ? make_int2(J, I) : make_int2(I, J);
+      if (lane == 0) {
+        E.kept_ij[slot] = tr ? make_int2(J, I) : make_int2(I, J);
+        count_kept(E.rowcnt, I, J);
+      }
     } else if (lane == 0) {
       atomicOr(E.overflow, 1);
     }

@@ -113,10 +113,17 @@ struct NumArgs {
   int* bad;                 // set when a NaN/Inf is produced
   double* partial;          // n_items x NQ
   unsigned long long* exec_pairs;  // block triples issued (all candidates)
+  int* rowcnt;              // nb: blocks kept per row (zeroed)
 };
 
 // Cluster row panels: for cluster P the sorted union of the columns K of its
 // atoms' rows, with the entry index of (I_s, K) for each member s (-1 absent).
+struct ClearArgs {        // integers set to 0
+  static constexpr int N = 6;
+  int* p[N];
+  long long n[N];
+};
+
 struct PanelArgs {
   int nc;
   const int* rp;
@@ -133,17 +140,18 @@ struct PanelArgs {
   int max_sys_clusters;
   // panels
   int* panel_cnt;         // nc
-  const int* panel_rp;    // nc+1
+  int* panel_rp;          // nc+1
   int* panel_k;
   int* panel_e;           // 8 per panel entry
   // tiles
   int* tile_cnt;          // nc
   long long* tile_pairs;  // nc: upper bound of output pairs of the tiles of P
-  const int* tile_rp;     // nc+1
+  int* tile_rp;           // nc+1
   int* tile_p;
   int* tile_q;
-  unsigned* tile_bits;    // nc x tile_words: cluster bitmap of pass 0 for pass 1
+  unsigned* tile_bits;    // nc x tile_words: cluster bitmap from k_panels for k_tiles
   int tile_words;         // (max_sys_clusters + 31) / 32
+  unsigned long long* nominal;  // per system: block triples of the full products (zeroed)
 };
 
 struct TileArgs {
@@ -202,6 +210,7 @@ struct TileArgs {
   int* bad;
   double* partial;        // n_tiles x NQ
   double* rows;           // trace sums per output, of an update in parts (tile_rows_bytes)
+  int* rowcnt;            // nb: blocks kept per row (zeroed)
   int fine_subs;          // most sub-tiles of an update in parts (at most FINE_SUBS)
   unsigned long long* exec_pairs;  // block products issued
 };
@@ -221,6 +230,7 @@ struct CopyArgs {
   int* stage_count;
   int stage_cap;
   int* overflow;
+  int* rowcnt;            // nb: blocks kept per row (zeroed)
 };
 
 struct CompactArgs {
@@ -228,7 +238,6 @@ struct CompactArgs {
   int D;
   const int* stage_count;
   const int2* kept_ij;
-  int* rowcnt;        // nb (zeroed)
   int* cursor;        // nb (zeroed)
   const int* new_rp;  // nb+1
   int* tmp_ci;
@@ -283,8 +292,10 @@ void launch_items(hipStream_t st, int nb, const int* cand_rp, const int* item_rp
 void launch_items_count(hipStream_t st, int nb, const int* cand_rp, int* item_cnt);
 void launch_numeric(hipStream_t st, int prec, const NumArgs& a);
 void launch_measure(hipStream_t st, int prec, const MeasArgs& a);
-void launch_panels(hipStream_t st, int pass, const PanelArgs& a);
-void launch_tiles(hipStream_t st, int pass, const PanelArgs& a);
+// clears, then panels and tile counts; tiles (and, for mult > 0, the systems' items)
+void launch_panels(hipStream_t st, const PanelArgs& a, const ClearArgs& clear);
+void launch_tiles(hipStream_t st, const PanelArgs& a, int mult, int* sys_lo, int* sys_hi);
+void launch_clear(hipStream_t st, const ClearArgs& a);
 bool launch_tile_numeric(hipStream_t st, int prec, const TileArgs& a);  // false: no such shape
 bool tile_shape_available(int kind, int D, int shape);
 int tile_shape_default(int kind, int D);
@@ -307,7 +318,6 @@ void launch_copy_through(hipStream_t st, int prec, const CopyArgs& a, int nnz);
 // nnz_dev (optional): the entry count on the device, at most nnz (the grid)
 void launch_block_norms(hipStream_t st, int prec, long long nnz, int D, const void* xv, float* bn,
                         const int* nnz_dev = nullptr);
-void launch_compact_count(hipStream_t st, const CompactArgs& a, int n_kept);
 void launch_compact_scatter(hipStream_t st, const CompactArgs& a, int n_kept);
 void launch_row_sort(hipStream_t st, const CompactArgs& a);
 // nnz_dev (optional): the new entry count on the device, at most nnz;

@@ -172,28 +172,41 @@ __global__ __launch_bounds__(256) void k_symbolic(int pass, SymArgs a) {
 
 // ------------------------------------------------------------------ scans
 // Exclusive scan of n ints into out[0..n] (out[n] = total), single block.
+// Exclusive sums of in[0 .. n) by one block, four values per thread at a time.
 __global__ __launch_bounds__(1024) void k_scan(int n, const int* in, int* out, int* total) {
-  __shared__ int s[1024];
-  __shared__ int carry;
-  if (threadIdx.x == 0) carry = 0;
-  __syncthreads();
-  for (int base = 0; base < n; base += 1024) {
-    int i = base + threadIdx.x;
-    int v = i < n ? in[i] : 0;
-    s[threadIdx.x] = v;
-    __syncthreads();
-    for (int o = 1; o < 1024; o <<= 1) {
-      int u = threadIdx.x >= o ? s[threadIdx.x - o] : 0;
-      __syncthreads();
-      s[threadIdx.x] += u;
-      __syncthreads();
+  __shared__ int sh[2][16];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  int carry = 0;
+  for (int base = 0, it = 0; base < n; base += 4096, it ^= 1) {
+    const int i = base + 4 * t;
+    int v[4], sum = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      v[k] = i + k < n ? in[i + k] : 0;
+      sum += v[k];
     }
-    if (i < n) out[i] = carry + s[threadIdx.x] - v;
+    int inc = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int u = __shfl_up(inc, o, 64);
+      inc += lane >= o ? u : 0;
+    }
+    if (lane == 63) sh[it][wave] = inc;
     __syncthreads();
-    if (threadIdx.x == 1023) carry += s[1023];
-    __syncthreads();
+    int at = carry + inc - sum;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+      const int x = sh[it][w];
+      at += w < wave ? x : 0;
+      carry += x;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (i + k < n) out[i + k] = at;
+      at += v[k];
+    }
   }
-  if (threadIdx.x == 0) {
+  if (t == 0) {
     out[n] = carry;
     if (total) *total = carry;
   }
@@ -252,7 +265,7 @@ __global__ __launch_bounds__(256) void k_numeric(NumArgs a) {
   const size_t stride = (size_t)(1 + D) * BS;
   EpiCtx E{a.xv, stride, a.h_rp, a.h_ci, a.h_v, {a.h1_rp[0], a.h1_rp[1], a.h1_rp[2]},
            {a.h1_ci[0], a.h1_ci[1], a.h1_ci[2]}, {a.h1_v[0], a.h1_v[1], a.h1_v[2]}, a.stage,
-           a.kept_ij, a.stage_count, a.stage_cap, a.overflow, a.bad};
+           a.kept_ij, a.stage_count, a.stage_cap, a.overflow, a.bad, a.rowcnt};
   double q[NQ];
 #pragma unroll
   for (int k = 0; k < NQ; ++k) q[k] = 0.0;
@@ -372,15 +385,6 @@ __global__ __launch_bounds__(64) void k_measure(MeasArgs a) {
 }
 
 // ------------------------------------------------------------------ compaction
-__global__ void k_compact_count(CompactArgs a, int n_kept) {
-  int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (a.n_kept_dev) n_kept = min(n_kept, *a.n_kept_dev);
-  if (k >= n_kept) return;
-  int2 ij = a.kept_ij[k];
-  atomicAdd(&a.rowcnt[ij.x], 1);
-  if (ij.y != ij.x) atomicAdd(&a.rowcnt[ij.y], 1);
-}
-
 __global__ void k_compact_scatter(CompactArgs a, int n_kept) {
   int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (a.n_kept_dev) n_kept = min(n_kept, *a.n_kept_dev);
@@ -534,6 +538,13 @@ __global__ void k_convert(long long n, const A* in, B* out) {
     out[i] = (B)in[i];
 }
 
+__global__ void k_clear(ClearArgs a) {
+  for (int k = 0; k < ClearArgs::N; ++k)
+    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < a.n[k];
+         i += (long long)gridDim.x * blockDim.x)
+      a.p[k][i] = 0;
+}
+
 __global__ void k_fill_int(int* p, int v, long long n) {
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (long long)gridDim.x * blockDim.x)
@@ -645,9 +656,11 @@ void launch_measure(hipStream_t st, int prec, const MeasArgs& a) {
   else measure_d<float>(st, a);
 }
 
-void launch_compact_count(hipStream_t st, const CompactArgs& a, int n_kept) {
-  if (n_kept == 0) return;
-  hipLaunchKernelGGL(k_compact_count, dim3(nblk(n_kept, 256)), dim3(256), 0, st, a, n_kept);
+void launch_clear(hipStream_t st, const ClearArgs& a) {
+  long long n = 0;
+  for (long long k : a.n) n = std::max(n, k);
+  if (n == 0) return;
+  hipLaunchKernelGGL(k_clear, dim3(sblk(n, 256)), dim3(256), 0, st, a);
 }
 
 void launch_compact_scatter(hipStream_t st, const CompactArgs& a, int n_kept) {

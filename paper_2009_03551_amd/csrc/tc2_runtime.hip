@@ -39,6 +39,19 @@ __global__ void k_nominal(int nb, const int* rp, const int* sys_of, const int* a
   }
 }
 
+// What the host reads after an update, into page-locked memory: [counters 32 B |
+// pairs 8 | new entries 8 | screen counts 16 | scalars].  One launch at the end
+// of the update in place of five copies of a few bytes at 7 us each.
+__global__ void k_report(const int* cnt, const unsigned long long* pairs, const int* nnz,
+                         const unsigned long long* screened, int n, const double* scal, char* out) {
+  const int t = threadIdx.x;
+  if (t < 8) ((int*)out)[t] = cnt[t];
+  if (t == 8) *(unsigned long long*)(out + 32) = *pairs;
+  if (t == 9) *(int*)(out + 40) = *nnz;
+  if (t >= 10 && t < 12 && screened) ((unsigned long long*)(out + 48))[t - 10] = screened[t - 10];
+  for (int i = t; i < n; i += blockDim.x) ((double*)(out + 64))[i] = scal[i];
+}
+
 }  // namespace
 
 
@@ -651,7 +664,6 @@ tc2_status step(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
   for (int s = 0; s < ctx->nsys; ++s) any_stopped |= !ctx->h_active[s];
 
   if (ctx->profile) HIPCHK(hipEventRecord(ctx->pev[0], st));
-  if (tc2_status r = count_nominal(ctx, st, ctx->rp[c].as<int>()); r != TC2_OK) return r;
   int n_work = 0;          // work items (atom path) or tile blocks (tiled path)
   long long out_bound = 0; // upper bound of computed output blocks
   const int kind = ctx->cur_prec == P_FP64 ? K_FP64
@@ -662,6 +674,7 @@ tc2_status step(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
   ctx->last_kind = kind;
   if (!tiled) {
     // ---- atom-level symbolic product and work items
+    if (tc2_status r = count_nominal(ctx, st, ctx->rp[c].as<int>()); r != TC2_OK) return r;
     HIPCHK(ctx->cand_cnt.reserve((size_t)nb * 4));
     HIPCHK(ctx->cand_rp.reserve((size_t)(nb + 1) * 4));
     SymArgs sa{};
@@ -728,29 +741,27 @@ tc2_status step(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
     pa.tile_words = (ctx->max_sys_clusters + 31) / 32;
     HIPCHK(ctx->tile_bits.reserve((size_t)std::max(nc, 1) * pa.tile_words * 4));
     pa.tile_bits = ctx->tile_bits.as<unsigned>();
-    launch_panels(st, 0, pa);
-    launch_scan(st, nc, ctx->panel_cnt.as<int>(), ctx->panel_rp.as<int>(), cnt);
-    HIPCHK(hipMemcpyAsync(hcnt, cnt, 4, hipMemcpyDeviceToHost, st));
-    HIPCHK(hipStreamSynchronize(st));
-    const int npanel = hcnt[0];
-    HIPCHK(ctx->panel_k.reserve((size_t)std::max(npanel, 1) * 4));
-    HIPCHK(ctx->panel_e.reserve((size_t)std::max(npanel, 1) * CS * 4));
+    // a panel column is that of at least one entry
+    const size_t ent = (size_t)std::max(ctx->nnz[c], 1);
+    HIPCHK(ctx->panel_k.reserve_grow(ent * 4));
+    HIPCHK(ctx->panel_e.reserve_grow(ent * CS * 4));
     pa.panel_k = ctx->panel_k.as<int>();
     pa.panel_e = ctx->panel_e.as<int>();
-    launch_panels(st, 1, pa);
-    launch_tiles(st, 0, pa);
-    launch_scan(st, nc, ctx->tile_cnt.as<int>(), ctx->tile_rp.as<int>(), cnt);
+    pa.nominal = ctx->nominal.as<unsigned long long>();
+    launch_panels(st, pa, ClearArgs{{ctx->nominal.as<int>()}, {2LL * ctx->nsys}});
     std::vector<long long> pairs(nc);
-    HIPCHK(hipMemcpyAsync(hcnt, cnt, 4, hipMemcpyDeviceToHost, st));
+    std::vector<int> tiles(nc);
+    HIPCHK(hipMemcpyAsync(tiles.data(), ctx->tile_cnt.p, (size_t)nc * 4, hipMemcpyDeviceToHost, st));
     HIPCHK(hipMemcpyAsync(pairs.data(), ctx->tile_pairs.p, (size_t)nc * 8, hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
-    const int ntiles = hcnt[0];
+    int ntiles = 0;
+    for (int v : tiles) ntiles += v;
     for (long long v : pairs) out_bound += v;
     HIPCHK(ctx->tile_p.reserve((size_t)std::max(ntiles, 1) * 4));
     HIPCHK(ctx->tile_q.reserve((size_t)std::max(ntiles, 1) * 4));
     pa.tile_p = ctx->tile_p.as<int>();
     pa.tile_q = ctx->tile_q.as<int>();
-    launch_tiles(st, 1, pa);
+    launch_tiles(st, pa, 0, nullptr, nullptr);  // the shape is not settled yet
     n_work = ntiles;
     HIPCHK(ctx->sys_lo.reserve((size_t)ctx->nsys * 4));
     HIPCHK(ctx->sys_hi.reserve((size_t)ctx->nsys * 4));
@@ -777,6 +788,8 @@ tc2_status step(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
     ctx->ms_sym += ms;
   }
   HIPCHK(ctx->exec_pairs.reserve(8));
+  HIPCHK(ctx->rowcnt.reserve((size_t)nb * 4));
+  HIPCHK(ctx->cursor.reserve((size_t)nb * 4));
   const bool screen = tiled && (ctx->skip_now != 0 || ctx->log_cap > 0);
   if (screen) {
     HIPCHK(ctx->bn.reserve((size_t)std::max(ctx->nnz[c], 1) * (1 + D) * 4));
@@ -827,6 +840,7 @@ tc2_status step(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
     ta.rows = ctx->sum_rows.as<double>();
     ta.fine_subs = ctx->test_fine_subs;
     ta.exec_pairs = ctx->exec_pairs.as<unsigned long long>();
+    ta.rowcnt = ctx->rowcnt.as<int>();
     ta.bf16 = (ctx->op_bf16 && ctx->cur_prec == P_FP32) ? 1 : 0;
     ta.wide = wide_now;
     ta.skip = ctx->skip_now;
@@ -909,8 +923,9 @@ tc2_status step(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
     int cap = (int)std::min<long long>(std::max<long long>(ctx->stage_cap, 1), out_bound > 0 ? out_bound : 1);
     HIPCHK(ctx->stage.reserve((size_t)cap * tile));
     HIPCHK(ctx->kept_ij.reserve((size_t)cap * 8));
-    launch_fill_int(st, cnt, 0, 8);
-    launch_fill_int(st, ctx->exec_pairs.as<int>(), 0, 2);
+    launch_clear(st, ClearArgs{{cnt, ctx->exec_pairs.as<int>(), ctx->rowcnt.as<int>(),
+                                ctx->cursor.as<int>(), screen ? ctx->screened.as<int>() : nullptr},
+                               {8, 2, nb, nb, screen ? 4 : 0}});
     if (ctx->profile) HIPCHK(hipEventRecord(ctx->pev[2], st));
     if (!tiled) {
       NumArgs na{};
@@ -946,10 +961,10 @@ tc2_status step(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
       na.bad = ctx->bad.as<int>();
       na.partial = ctx->partial.as<double>();
       na.exec_pairs = ctx->exec_pairs.as<unsigned long long>();
+      na.rowcnt = ctx->rowcnt.as<int>();
       launch_numeric(st, ctx->cur_prec, na);
     } else {
       TileArgs ta = tile_args(cap, ctx->shape[kind]);
-      if (screen) launch_fill_int(st, ctx->screened.as<int>(), 0, 4);
       if (!launch_tile_numeric(st, ctx->cur_prec, ta)) return TC2_EINVAL;
     }
     HIPCHK(hipGetLastError());
@@ -968,6 +983,7 @@ tc2_status step(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
       ca.stage_count = cnt + 1;
       ca.stage_cap = cap;
       ca.overflow = cnt + 2;
+      ca.rowcnt = ctx->rowcnt.as<int>();
       launch_copy_through(st, ctx->cur_prec, ca, ctx->nnz[c]);
       HIPCHK(hipGetLastError());
     }
@@ -1025,23 +1041,17 @@ tc2_status step(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
 
   // ---- compaction into the new pattern
   if (ctx->profile) HIPCHK(hipEventRecord(ctx->pev[0], st));
-  HIPCHK(ctx->rowcnt.reserve((size_t)nb * 4));
-  HIPCHK(ctx->cursor.reserve((size_t)nb * 4));
   HIPCHK(ctx->rp[n].reserve((size_t)(nb + 1) * 4));
-  launch_fill_int(st, ctx->rowcnt.as<int>(), 0, nb);
-  launch_fill_int(st, ctx->cursor.as<int>(), 0, nb);
   CompactArgs ca{};
   ca.nb = nb;
   ca.D = D;
   ca.kept_ij = ctx->kept_ij.as<int2>();
-  ca.rowcnt = ctx->rowcnt.as<int>();
   ca.cursor = ctx->cursor.as<int>();
   ca.new_rp = ctx->rp[n].as<int>();
   ca.sys_of = ctx->sys_of.as<int>();
   ca.sys_start = ctx->sys_start.as<int>();
   ca.sys_end = ctx->sys_end.as<int>();
   ca.max_sys_atoms = ctx->max_sys_atoms;
-  launch_compact_count(st, ca, n_kept);
   launch_scan(st, nb, ctx->rowcnt.as<int>(), ctx->rp[n].as<int>(), cnt);
   HIPCHK(hipMemcpyAsync(hcnt, cnt, 4, hipMemcpyDeviceToHost, st));
   HIPCHK(hipStreamSynchronize(st));
@@ -1237,10 +1247,9 @@ int step_graph(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
         (uintptr_t)ctx->sys_hi.p, (uintptr_t)ctx->panel_cnt.p, (uintptr_t)ctx->panel_rp.p,
         (uintptr_t)ctx->tile_cnt.p, (uintptr_t)ctx->tile_rp.p, (uintptr_t)ctx->tile_pairs.p,
         (uintptr_t)ctx->tile_bits.p, (uintptr_t)ctx->nominal.p, (uintptr_t)ctx->mask[c].p,
-        (uintptr_t)ctx->mask[n].p, (uintptr_t)ctx->sum_rows.p};
+        (uintptr_t)ctx->mask[n].p, (uintptr_t)ctx->sum_rows.p, (uintptr_t)ctx->pin_graph.p};
     // the three parts of the update, as stream work (captured or not)
     auto rec_pre = [&]() {
-      (void)count_nominal(ctx, st, ctx->rp[c].as<int>());
       PanelArgs pa{};
       pa.nc = nc;
       pa.rp = ctx->rp[c].as<int>();
@@ -1266,22 +1275,16 @@ int step_graph(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
       pa.tile_q = ctx->tile_q.as<int>();
       pa.tile_bits = ctx->tile_bits.as<unsigned>();
       pa.tile_words = tile_words;
-      launch_panels(st, 0, pa);
-      launch_scan(st, nc, ctx->panel_cnt.as<int>(), ctx->panel_rp.as<int>(), cnt);
-      launch_panels(st, 1, pa);
-      launch_tiles(st, 0, pa);
-      launch_scan(st, nc, ctx->tile_cnt.as<int>(), ctx->tile_rp.as<int>(), cnt);
-      launch_tiles(st, 1, pa);
-      launch_sys_items(st, ctx->nsys, mult, ctx->csys_start.as<int>(), ctx->csys_end.as<int>(),
-                       ctx->tile_rp.as<int>(), ctx->sys_lo.as<int>(), ctx->sys_hi.as<int>());
-      if (screen) {
-        launch_fill_int(st, ctx->screened.as<int>(), 0, 4);
-        if (!norms_ready)
-          launch_block_norms(st, ctx->cur_prec, cap_c, D, ctx->xv[c].p, ctx->bn.as<float>(),
-                             ctx->rp[c].as<int>() + nb);
-      }
-      launch_fill_int(st, cnt, 0, 8);
-      launch_fill_int(st, ctx->exec_pairs.as<int>(), 0, 2);
+      pa.nominal = ctx->nominal.as<unsigned long long>();
+      launch_panels(st, pa,
+                    ClearArgs{{cnt, ctx->exec_pairs.as<int>(), ctx->rowcnt.as<int>(),
+                               ctx->cursor.as<int>(), ctx->nominal.as<int>(),
+                               screen ? ctx->screened.as<int>() : nullptr},
+                              {8, 2, nb, nb, 2LL * ctx->nsys, screen ? 4 : 0}});
+      launch_tiles(st, pa, mult, ctx->sys_lo.as<int>(), ctx->sys_hi.as<int>());
+      if (screen && !norms_ready)
+        launch_block_norms(st, ctx->cur_prec, cap_c, D, ctx->xv[c].p, ctx->bn.as<float>(),
+                           ctx->rp[c].as<int>() + nb);
     };
     auto rec_num = [&]() -> bool {
       TileArgs ta{};
@@ -1321,6 +1324,7 @@ int step_graph(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
       ta.rows = ctx->sum_rows.as<double>();
       ta.fine_subs = ctx->test_fine_subs;
       ta.exec_pairs = ctx->exec_pairs.as<unsigned long long>();
+      ta.rowcnt = ctx->rowcnt.as<int>();
       ta.bf16 = (ctx->op_bf16 && ctx->cur_prec == P_FP32) ? 1 : 0;
       ta.wide = kind == K_WIDE ? 1 : 0;
       ta.shape = shape;
@@ -1348,15 +1352,13 @@ int step_graph(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
         ca.stage_count = cnt + 1;
         ca.stage_cap = cap;
         ca.overflow = cnt + 2;
+        ca.rowcnt = ctx->rowcnt.as<int>();
         launch_copy_through(st, ctx->cur_prec, ca, (int)cap_c);
       }
-      launch_fill_int(st, ctx->rowcnt.as<int>(), 0, nb);
-      launch_fill_int(st, ctx->cursor.as<int>(), 0, nb);
       CompactArgs cm{};
       cm.nb = nb;
       cm.D = D;
       cm.kept_ij = ctx->kept_ij.as<int2>();
-      cm.rowcnt = ctx->rowcnt.as<int>();
       cm.cursor = ctx->cursor.as<int>();
       cm.new_rp = ctx->rp[n].as<int>();
       cm.sys_of = ctx->sys_of.as<int>();
@@ -1368,7 +1370,6 @@ int step_graph(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
       cm.tmp_src = ctx->tmp_src.as<int>();
       cm.new_ci = ctx->ci[n].as<int>();
       cm.new_src = ctx->new_src.as<int>();
-      launch_compact_count(st, cm, cap);
       launch_scan(st, nb, ctx->rowcnt.as<int>(), ctx->rp[n].as<int>(), cnt);
       launch_compact_scatter(st, cm, cap);
       launch_row_sort(st, cm);
@@ -1399,6 +1400,11 @@ int step_graph(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
         da.branch = ctx->branch.as<int>();
         da.word = ctx->dl_word.as<DecideWord>();
         launch_decide(st, da);
+      } else {
+        hipLaunchKernelGGL(k_report, dim3(1), dim3(256), 0, st, cnt,
+                           ctx->exec_pairs.as<unsigned long long>(), ctx->rp[n].as<int>() + nb,
+                           screen ? ctx->screened.as<unsigned long long>() : nullptr, ctx->nsys * NQ,
+                           ctx->scal.as<double>(), (char*)ctx->pin_graph.p);
       }
     };
     // capture of a part sequence into an executable graph; false if refused
@@ -1467,15 +1473,10 @@ int step_graph(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
       ctx->bn_valid = screen;
       return TC2_OK;
     }
-    // counters, pairs, new entries, screen counts and scalars, read back
-    // through page-locked memory: [hcnt 32 B | pairs 8 | nnz_new 8 | sc 16 | scal]
+    // counters, pairs, new entries, screen counts and scalars, written to
+    // page-locked memory by the update (k_report)
     scal.resize((size_t)ctx->nsys * NQ);
-    char* pin = (char*)ctx->pin_graph.p;
-    HIPCHK(hipMemcpyAsync(pin, cnt, sizeof(hcnt), hipMemcpyDeviceToHost, st));
-    HIPCHK(hipMemcpyAsync(pin + 32, ctx->exec_pairs.p, 8, hipMemcpyDeviceToHost, st));
-    HIPCHK(hipMemcpyAsync(pin + 40, ctx->rp[n].as<int>() + nb, 4, hipMemcpyDeviceToHost, st));
-    if (screen) HIPCHK(hipMemcpyAsync(pin + 48, ctx->screened.p, 16, hipMemcpyDeviceToHost, st));
-    HIPCHK(hipMemcpyAsync(pin + 64, ctx->scal.p, scal.size() * 8, hipMemcpyDeviceToHost, st));
+    const char* pin = (const char*)ctx->pin_graph.p;
     HIPCHK(hipStreamSynchronize(st));
     memcpy(hcnt, pin, sizeof(hcnt));
     memcpy(&pairs, pin + 32, 8);

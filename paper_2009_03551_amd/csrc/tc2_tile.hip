@@ -12,166 +12,229 @@
 #include "tc2_device.h"
 #include "tc2_tile.h"
 
+#include <algorithm>
+
 namespace tc2 {
 
 // ------------------------------------------------------------------ cluster panels
+// The symbolic part of an update is three launches (k_panel_count, k_panels,
+// k_tiles), each with a block per cluster: of the 230 us of an update of a small
+// system (64-atom chain) 130 went to its 23 small kernels, at 4 us or more
+// each, so counters are cleared and offsets found by the kernels that need
+// them.  A block adds the counts of the clusters before its own itself (nc
+// integers from L2) where a scan would be a launch between two others.
+//
 // Panel of cluster P: sorted union of the columns of its atoms' rows, with the
 // entry index of (I_s, K) for every member s (-1 when absent).  The union is
-// an LDS bitmap over the system's atoms; pass 1 ranks each member entry in it
+// an LDS bitmap over the system's atoms; k_panels ranks each member entry in it
 // (prefix popcounts), so no search is needed.
-constexpr int PNT = 1024;  // threads of the panel and tile kernels
+constexpr int PNT = 1024;         // threads of the panel and tile kernels
+constexpr int PNW = PNT / 64;     // waves
+static_assert(PNW % CS == 0, "waves split evenly over the members of a cluster");
 
-__device__ __forceinline__ int block_exclusive_scan(int v, int* ssc) {
-  const int t = threadIdx.x;
-  ssc[t] = v;
-  __syncthreads();
-  for (int o = 1; o < PNT; o <<= 1) {
-    const int u = (t >= o) ? ssc[t - o] : 0;
-    __syncthreads();
-    ssc[t] += u;
-    __syncthreads();
-  }
-  return ssc[t] - v;  // ssc[PNT-1] holds the total
-}
-
-__global__ __launch_bounds__(PNT) void k_panels(int pass, PanelArgs a) {
-  extern __shared__ unsigned sbits[];  // nwords bits, then nwords prefix counts
-  __shared__ int sscan[PNT];
-  const int P = blockIdx.x;
-  const int sys = a.clus_sys[P];
-  const int t = threadIdx.x;
-  if (!a.active[sys]) {
-    if (pass == 0 && t == 0) a.panel_cnt[P] = 0;
-    return;
-  }
-  const int lo = a.sys_start[sys], nbits = a.sys_end[sys] - lo;
-  const int nwords = (nbits + 31) >> 5;
-  unsigned* pre = sbits + nwords;
-  for (int w = t; w < nwords; w += PNT) sbits[w] = 0u;
-  __syncthreads();
-  for (int s = 0; s < CS; ++s) {
-    const int I = a.clus_atom[P * CS + s];
-    if (I < 0) continue;
-    for (int e = a.rp[I] + t; e < a.rp[I + 1]; e += PNT) {
-      const int o = a.ci[e] - lo;
-      atomicOr(&sbits[o >> 5], 1u << (o & 31));
-    }
-  }
-  __syncthreads();
-  const int per = (nwords + PNT - 1) / PNT;
-  const int w0 = t * per, w1 = min(nwords, w0 + per);
-  int cnt = 0;
-  for (int w = w0; w < w1; ++w) cnt += __popc(sbits[w]);
-  const int before = block_exclusive_scan(cnt, sscan);
-  if (pass == 0) {
-    if (t == PNT - 1) a.panel_cnt[P] = sscan[PNT - 1];
-    return;
-  }
-  const int base = a.panel_rp[P];
-  int run = before;
-  for (int w = w0; w < w1; ++w) {
-    pre[w] = run;
-    unsigned x = sbits[w];
-    while (x) {
-      const int bit = __ffs(x) - 1;
-      x &= x - 1;
-      const int pos = base + run++;
-      a.panel_k[pos] = lo + (w << 5) + bit;
+// sum of v over the threads before this one; *total: over all (sh: PNW ints)
+__device__ __forceinline__ int block_exclusive_scan(int v, int* sh, int* total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int inc = v;
 #pragma unroll
-      for (int s = 0; s < CS; ++s) a.panel_e[(size_t)pos * CS + s] = -1;
-    }
+  for (int o = 1; o < 64; o <<= 1) {
+    const int u = __shfl_up(inc, o, 64);
+    inc += lane >= o ? u : 0;
   }
-  __syncthreads();  // ranks in LDS and the -1 fill precede the entry writes
-  for (int s = 0; s < CS; ++s) {
-    const int I = a.clus_atom[P * CS + s];
-    if (I < 0) continue;
-    for (int e = a.rp[I] + t; e < a.rp[I + 1]; e += PNT) {
-      const int o = a.ci[e] - lo, w = o >> 5;
-      const int rank = (int)pre[w] + __popc(sbits[w] & ((1u << (o & 31)) - 1u));
-      a.panel_e[(size_t)(base + rank) * CS + s] = e;
-    }
+  __syncthreads();  // readers of sh are done
+  if (lane == 63) sh[wave] = inc;
+  __syncthreads();
+  int before = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < PNW; ++w) {
+    const int x = sh[w];
+    before += w < wave ? x : 0;
+    all += x;
   }
+  *total = all;
+  return before + inc - v;
 }
 
-// Tiles of cluster P: the clusters Q >= P holding an atom J with a column K in
-// common with some atom of P (cluster-level symbolic product).  Pass 0 builds
-// the cluster bitmap, keeps it in tile_bits and bounds the number of output
-// blocks of the tiles; pass 1 writes the tiles from the kept bitmap.
-__global__ __launch_bounds__(PNT) void k_tiles(int pass, PanelArgs a) {
+// sum of cnt[0 .. P)
+__device__ __forceinline__ int sum_before(const int* cnt, int P, int* sh) {
+  int v = 0, total = 0;
+  for (int i = threadIdx.x; i < P; i += PNT) v += cnt[i];
+  (void)block_exclusive_scan(v, sh, &total);
+  return total;
+}
+
+// f(entry, member) for the entries of the rows of cluster P, members side by side
+template <typename F>
+__device__ __forceinline__ void each_entry(const PanelArgs& a, int P, F&& f) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, s = wave % CS;
+  const int I = a.clus_atom[P * CS + s];
+  if (I < 0) return;
+  const int end = a.rp[I + 1];
+  for (int e = a.rp[I] + (wave / CS) * 64 + lane; e < end; e += PNT / CS) f(e, s);
+}
+
+// the LDS bitmap of the union; its words [w0, w1) belong to this thread
+__device__ __forceinline__ void panel_bits(const PanelArgs& a, int P, int lo, int nwords, unsigned* bits) {
+  for (int w = threadIdx.x; w < nwords; w += PNT) bits[w] = 0u;
+  __syncthreads();
+  each_entry(a, P, [&](int e, int) {
+    const int o = a.ci[e] - lo;
+    atomicOr(&bits[o >> 5], 1u << (o & 31));
+  });
+  __syncthreads();
+}
+
+// Columns of every panel; clears the counters of the update.
+__global__ __launch_bounds__(PNT) void k_panel_count(PanelArgs a, ClearArgs clear) {
   extern __shared__ unsigned sbits[];
-  __shared__ int sscan[PNT];
-  __shared__ long long spairs[PNT];
+  __shared__ int sh[PNW];
   const int P = blockIdx.x;
   const int sys = a.clus_sys[P];
   const int t = threadIdx.x;
+#pragma unroll
+  for (int k = 0; k < ClearArgs::N; ++k)
+    for (long long i = (long long)P * PNT + t; i < clear.n[k]; i += (long long)gridDim.x * PNT)
+      clear.p[k][i] = 0;
   if (!a.active[sys]) {
-    if (pass == 0 && t == 0) {
+    if (t == 0) a.panel_cnt[P] = 0;
+    return;
+  }
+  const int lo = a.sys_start[sys], nwords = (a.sys_end[sys] - lo + 31) >> 5;
+  panel_bits(a, P, lo, nwords, sbits);
+  int cnt = 0, total = 0;
+  for (int w = t; w < nwords; w += PNT) cnt += __popc(sbits[w]);
+  (void)block_exclusive_scan(cnt, sh, &total);
+  if (t == 0) a.panel_cnt[P] = total;
+}
+
+// Panels, the triples of the full products (nominal, cleared before), and the
+// clusters Q >= P holding an atom J with a column K in common with some atom of
+// P (cluster-level symbolic product): their bitmap (tile_bits), count and a
+// bound of the number of output blocks of their tiles.
+__global__ __launch_bounds__(PNT) void k_panels(PanelArgs a) {
+  extern __shared__ unsigned sbits[];  // nwords bits and nwords prefix counts, then the tiles' bits
+  __shared__ int sh[PNW];
+  __shared__ long long spairs[PNW];
+  const int P = blockIdx.x;
+  const int sys = a.clus_sys[P];
+  const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
+  const int base = sum_before(a.panel_cnt, P, sh);
+  const int np = a.panel_cnt[P];
+  if (t == 0) {
+    a.panel_rp[P] = base;
+    if (P == a.nc - 1) a.panel_rp[a.nc] = base + np;
+  }
+  if (!a.active[sys]) {
+    if (t == 0) {
       a.tile_cnt[P] = 0;
       a.tile_pairs[P] = 0;
     }
     return;
   }
-  const int nbits = a.csys_end[sys] - P;
-  const int nwords = (nbits + 31) >> 5;
-  unsigned* gbits = a.tile_bits + (size_t)P * a.tile_words;
-  if (pass == 0) {
-    for (int w = t; w < nwords; w += PNT) sbits[w] = 0u;
-    __syncthreads();
-    const int wave = t >> 6, lane = t & 63, nw = PNT >> 6;
-    for (int idx = a.panel_rp[P] + wave; idx < a.panel_rp[P + 1]; idx += nw) {
-      const int K = a.panel_k[idx];
-      for (int f = a.rp[K] + lane; f < a.rp[K + 1]; f += 64) {
-        const int Q = a.atom_clus[a.ci[f]];
-        if (Q >= P) {
-          const int o = Q - P;
-          atomicOr(&sbits[o >> 5], 1u << (o & 31));
-        }
-      }
-    }
-    __syncthreads();
-    for (int w = t; w < nwords; w += PNT) gbits[w] = sbits[w];
-  } else {
-    for (int w = t; w < nwords; w += PNT) sbits[w] = gbits[w];
-    __syncthreads();
-  }
-  const int per = (nwords + PNT - 1) / PNT;
-  const int w0 = t * per, w1 = min(nwords, w0 + per);
-  int cnt = 0;
-  for (int w = w0; w < w1; ++w) cnt += __popc(sbits[w]);
-  if (pass == 0) {
-    int nP = 0;
-    for (int s = 0; s < CS; ++s) nP += a.clus_atom[P * CS + s] >= 0;
-    long long pairs = 0;
+  const int lo = a.sys_start[sys], nwords = (a.sys_end[sys] - lo + 31) >> 5;
+  unsigned* pre = sbits + nwords;
+  panel_bits(a, P, lo, nwords, sbits);
+  {
+    const int per = (nwords + PNT - 1) / PNT;
+    const int w0 = t * per, w1 = min(nwords, w0 + per);
+    int cnt = 0, total = 0;
+    for (int w = w0; w < w1; ++w) cnt += __popc(sbits[w]);
+    int run = block_exclusive_scan(cnt, sh, &total);
     for (int w = w0; w < w1; ++w) {
+      pre[w] = run;
       unsigned x = sbits[w];
       while (x) {
         const int bit = __ffs(x) - 1;
         x &= x - 1;
-        const int Q = P + (w << 5) + bit;
-        int nQ = 0;
-        for (int s = 0; s < CS; ++s) nQ += a.clus_atom[Q * CS + s] >= 0;
-        pairs += (Q == P) ? (long long)nP * (nP + 1) / 2 : (long long)nP * nQ;
+        const int pos = base + run++;
+        a.panel_k[pos] = lo + (w << 5) + bit;
       }
     }
-    sscan[t] = cnt;
-    spairs[t] = pairs;
-    __syncthreads();
-    for (int o = PNT / 2; o > 0; o >>= 1) {
-      if (t < o) {
-        sscan[t] += sscan[t + o];
-        spairs[t] += spairs[t + o];
-      }
-      __syncthreads();
-    }
-    if (t == 0) {
-      a.tile_cnt[P] = sscan[0];
-      a.tile_pairs[P] = spairs[0];
-    }
-    return;
   }
-  int pos = a.tile_rp[P] + block_exclusive_scan(cnt, sscan);
+  for (int i = t; i < np * CS; i += PNT) a.panel_e[(size_t)base * CS + i] = -1;
+  if (wave == 0) {
+    const int I = lane < CS ? a.clus_atom[P * CS + lane] : -1;
+    const unsigned long long m = I >= 0 ? (unsigned long long)(a.rp[I + 1] - a.rp[I]) : 0ull;
+    unsigned long long sum = m * m;
+#pragma unroll
+    for (int o = CS / 2; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    if (lane == 0) atomicAdd(&a.nominal[sys], sum);
+  }
+  __syncthreads();  // ranks, columns and the -1 fill precede their readers
+  each_entry(a, P, [&](int e, int s) {
+    const int o = a.ci[e] - lo, w = o >> 5;
+    const int rank = (int)pre[w] + __popc(sbits[w] & ((1u << (o & 31)) - 1u));
+    a.panel_e[(size_t)(base + rank) * CS + s] = e;
+  });
+  __syncthreads();  // the ranks are no longer needed
+  unsigned* tbits = sbits;
+  const int twords = (a.csys_end[sys] - P + 31) >> 5;
+  for (int w = t; w < twords; w += PNT) tbits[w] = 0u;
+  __syncthreads();
+  for (int idx = wave; idx < np; idx += PNW) {
+    const int K = a.panel_k[base + idx];
+    for (int f = a.rp[K] + lane; f < a.rp[K + 1]; f += 64) {
+      const int Q = a.atom_clus[a.ci[f]];
+      if (Q >= P) {
+        const int o = Q - P;
+        atomicOr(&tbits[o >> 5], 1u << (o & 31));
+      }
+    }
+  }
+  __syncthreads();
+  int nP = 0;
+  for (int s = 0; s < CS; ++s) nP += a.clus_atom[P * CS + s] >= 0;
+  int cnt = 0, total = 0;
+  long long pairs = 0;
+  for (int w = t; w < twords; w += PNT) {
+    unsigned x = tbits[w];
+    a.tile_bits[(size_t)P * a.tile_words + w] = x;
+    cnt += __popc(x);
+    while (x) {
+      const int bit = __ffs(x) - 1;
+      x &= x - 1;
+      const int Q = P + (w << 5) + bit;
+      int nQ = 0;
+      for (int s = 0; s < CS; ++s) nQ += a.clus_atom[Q * CS + s] >= 0;
+      pairs += (Q == P) ? (long long)nP * (nP + 1) / 2 : (long long)nP * nQ;
+    }
+  }
+  for (int o = 32; o > 0; o >>= 1) pairs += __shfl_xor(pairs, o, 64);
+  if (lane == 0) spairs[wave] = pairs;
+  (void)block_exclusive_scan(cnt, sh, &total);  // spairs is complete behind its barriers
+  if (t == 0) {
+    long long all = 0;
+    for (int w = 0; w < PNW; ++w) all += spairs[w];
+    a.tile_cnt[P] = total;
+    a.tile_pairs[P] = all;
+  }
+}
+
+// The tiles of cluster P from its bitmap, and (mult > 0) the range of work
+// items, mult per tile, of every system.
+__global__ __launch_bounds__(PNT) void k_tiles(PanelArgs a, int mult, int* sys_lo, int* sys_hi) {
+  __shared__ int sh[PNW];
+  const int P = blockIdx.x;
+  const int sys = a.clus_sys[P];
+  const int t = threadIdx.x;
+  const int base = sum_before(a.tile_cnt, P, sh);
+  if (t == 0) {
+    const int end = base + a.tile_cnt[P];
+    a.tile_rp[P] = base;
+    if (P == a.nc - 1) a.tile_rp[a.nc] = end;
+    if (mult > 0 && P == a.csys_start[sys]) sys_lo[sys] = mult * base;
+    if (mult > 0 && P == a.csys_end[sys] - 1) sys_hi[sys] = mult * end;
+  }
+  if (!a.active[sys]) return;
+  const int nwords = (a.csys_end[sys] - P + 31) >> 5;
+  const unsigned* bits = a.tile_bits + (size_t)P * a.tile_words;
+  const int per = (nwords + PNT - 1) / PNT;
+  const int w0 = t * per, w1 = min(nwords, w0 + per);
+  int cnt = 0, total = 0;
+  for (int w = w0; w < w1; ++w) cnt += __popc(bits[w]);
+  int pos = base + block_exclusive_scan(cnt, sh, &total);
   for (int w = w0; w < w1; ++w) {
-    unsigned x = sbits[w];
+    unsigned x = bits[w];
     while (x) {
       const int bit = __ffs(x) - 1;
       x &= x - 1;
@@ -215,7 +278,10 @@ __global__ void k_copy_through(CopyArgs a) {
       const int r = qq >> 4, c = qq & 15;
       st[q] = X[m * BS + c * BP + r];
     }
-    if (lane == 0) a.kept_ij[slot] = make_int2(I, J);
+    if (lane == 0) {
+      a.kept_ij[slot] = make_int2(I, J);
+      count_kept(a.rowcnt, I, J);
+    }
   }
 }
 
@@ -258,16 +324,17 @@ void launch_block_norms(hipStream_t st, int prec, long long nnz, int D, const vo
 }
 
 // ================================================================== launchers
-void launch_panels(hipStream_t st, int pass, const PanelArgs& a) {
+void launch_panels(hipStream_t st, const PanelArgs& a, const ClearArgs& clear) {
   if (a.nc == 0) return;
-  const size_t lds = (size_t)((a.max_sys_atoms + 31) / 32) * 8;  // bitmap + prefix counts
-  hipLaunchKernelGGL(k_panels, dim3(a.nc), dim3(PNT), lds, st, pass, a);
+  const size_t words = (size_t)((a.max_sys_atoms + 31) / 32);
+  hipLaunchKernelGGL(k_panel_count, dim3(a.nc), dim3(PNT), words * 4, st, a, clear);
+  hipLaunchKernelGGL(k_panels, dim3(a.nc), dim3(PNT), std::max(2 * words, (size_t)a.tile_words) * 4, st,
+                     a);
 }
 
-void launch_tiles(hipStream_t st, int pass, const PanelArgs& a) {
+void launch_tiles(hipStream_t st, const PanelArgs& a, int mult, int* sys_lo, int* sys_hi) {
   if (a.nc == 0) return;
-  const size_t lds = (size_t)a.tile_words * 4;
-  hipLaunchKernelGGL(k_tiles, dim3(a.nc), dim3(PNT), lds, st, pass, a);
+  hipLaunchKernelGGL(k_tiles, dim3(a.nc), dim3(PNT), 0, st, a, mult, sys_lo, sys_hi);
 }
 
 bool tile_shape_available(int kind, int D, int shape) {

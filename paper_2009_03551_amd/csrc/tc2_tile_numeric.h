@@ -836,7 +836,7 @@ __device__ __forceinline__ void tile_numeric() {
       k = kargs();
       EpiCtx E{k->xv, (size_t)PER, k->h_rp, k->h_ci, k->h_v, {k->h1_rp[0], k->h1_rp[1], k->h1_rp[2]},
                {k->h1_ci[0], k->h1_ci[1], k->h1_ci[2]}, {k->h1_v[0], k->h1_v[1], k->h1_v[2]}, k->stage,
-               k->kept_ij, k->stage_count, k->stage_cap, k->overflow, k->bad};
+               k->kept_ij, k->stage_count, k->stage_cap, k->overflow, k->bad, k->rowcnt};
 #pragma unroll
       for (int o = 0; o < NO; ++o) {
         if (!((own_mask >> o) & 1u)) continue;
@@ -899,8 +899,20 @@ __global__ __launch_bounds__(256) void k_sub_sums(TileArgs a, int go) {
   static_assert(NQ <= 16, "a lane per sum");
   const int total = (a.n_tiles_dev ? *a.n_tiles_dev : a.n_tiles) * SUBS;
   const int q = threadIdx.x & 15, lb = blockIdx.x * 16 + (threadIdx.x >> 4);
-  if (total <= a.fine_subs && lb < total && q < NQ)
-    a.partial[(size_t)lb * NQ + q] = sub_sum(a.rows + (size_t)lb * NOUT * NQ + q, NOUT / go, go);
+  if (total > a.fine_subs || lb >= total || q >= NQ) return;
+  double v[NOUT];  // all rows in flight at once
+#pragma unroll
+  for (int o = 0; o < NOUT; ++o) v[o] = a.rows[((size_t)lb * NOUT + o) * NQ + q];
+  double sum = 0.0, part = 0.0;  // as sub_sum
+#pragma unroll
+  for (int o = 0; o < NOUT; ++o) {
+    part += v[o];
+    if ((o + 1) % go == 0) {
+      sum += part;
+      part = 0.0;
+    }
+  }
+  a.partial[(size_t)lb * NQ + q] = sum;
 }
 
 // ================================================================== launch

@@ -350,3 +350,18 @@ def test_parts_of_a_subtile_equal_the_subtile(knob, case):
     for x, y in zip([a.X0] + a.X1, [b.X0] + b.X1):
         assert np.array_equal(x.row_ptr, y.row_ptr) and np.array_equal(x.col, y.col)
         assert np.array_equal(x.val, y.val)
+
+
+@pytest.mark.parametrize("n,graph", [(4090, False), (9003, False), (9003, True)])
+def test_panels_of_many_clusters(n, graph):
+    # more than 1024 clusters and 4096 rows: offsets and row starts summed in
+    # several rounds; the one-wave-per-block kernel needs no panels, and counts
+    # the triples of the full products from the rows
+    s = W.config_system("chain64", n=n, b=2, occ=1, eps=1e-5, seed=11)
+    a = T.solve(s, graph=graph)[0]
+    b = T.solve(s, kernel="block")[0]
+    print(f"  n={n}: {a.status_name} {a.iters} updates", flush=True)
+    assert a.branches == b.branches and a.nominal_flops == b.nominal_flops
+    for x, y in zip([a.X0] + a.X1, [b.X0] + b.X1):
+        assert np.array_equal(x.row_ptr, y.row_ptr) and np.array_equal(x.col, y.col)
+        assert np.abs(x.val - y.val).max() < FP64_X
