@@ -29,7 +29,7 @@ namespace tc2 {
 //
 // Measured (MI355X).  Reading the operands from global memory instead (no LDS,
 // no barrier) is bound by the fabric behind L2 (9.7 TB/s of operands): 877 ms
-// per solve of a 1728-atom lattice in three directions, against 691 here; the
+// per solve of a 1728-atom lattice in three directions, against 677 here; the
 // kernel before, a column and two barriers at a time in blocks of 16 x 16 with
 // every matrix of a present block staged, took 1001.  What remains: an FP64 or
 // FP32 MFMA leaves no issue slot to the vector ALU of its SIMD (measured with
@@ -37,7 +37,10 @@ namespace tc2 {
 // vector time (3.6 instructions per MFMA, about 100) add up; the rest is waits
 // of a stage for its busiest wave (1.5 times the mean) and for copies of columns
 // too large to stand in the ring beside the stage in use.  Hence the packed
-// plan words, scalar addresses and arguments read where they are used.
+// plan words, scalar addresses and arguments read where they are used, and
+// fragments read without conditions, four to eight reads in flight (with
+// conditions the compiler waited at each: 688 ms, and 346 instead of 333 for
+// 1000 atoms in one direction).
 // Sub-tiles dealt to the XCDs in chunks (L2 hits 10 -> 17 %) and half the blocks
 // per CU (-40 %) did not help.
 typedef float f2v __attribute__((ext_vector_type(2)));
@@ -45,11 +48,16 @@ typedef float f4v __attribute__((ext_vector_type(4)));
 typedef int i2v __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) void lds_void;
 
-constexpr int KLMAX = 1024;   // common columns held in LDS per pass over P's panel
+constexpr int KLMAX_ALL = 2048;  // most common columns held in LDS per pass over P's panel
 constexpr int KLQ_BITS = 20;  // kl: offset in the pass (12 bits) | offset in Q's panel (20 bits)
-static_assert((1 << (32 - KLQ_BITS)) >= KLMAX && (1 << KLQ_BITS) >= MAX_SYS_BITS, "kl packing");
-constexpr int NWB = 8;        // waves per block
-constexpr int LDS_BLOCK = 160 * 1024 / 2;  // two blocks share a CU
+static_assert((1 << (32 - KLQ_BITS)) >= KLMAX_ALL && (1 << KLQ_BITS) >= MAX_SYS_BITS, "kl packing");
+// Waves per block.  With at most one direction a block of 16 waves has a CU to
+// itself and computes a whole sub-tile, 8 x 8 outputs, at a time: columns are
+// planned and copied once for all of them (1000-atom lattice in one direction
+// 333 -> 320 ms).  With more, an output has 7 products per column, a stage lasts
+// longer than its waits, and two blocks of 8 waves fill each other's gaps (1728
+// atoms in three directions: 677 ms, with 16 waves 769).
+constexpr int waves(bool fine, int D) { return fine || D >= 2 ? 8 : 16; }
 
 // the 1 + D block norms of an entry
 template <int D>
@@ -137,12 +145,14 @@ __device__ __forceinline__ void tile_numeric() {
   auto sum_row = [&](int r, int q) { return ((r / GO) * TQ + (q + TQ - r % TQ) % TQ) * GO + r % GO; };
   constexpr int SUBS = (CS / SP) * (CS / TQ);
   // part of a sub-tile in work at a time: with two or more directions 4 x 4
-  // outputs, two per wave (64 accumulator registers in FP64), else 4 x 8, four
-  constexpr int PS = FINE ? 2 : 4, PT = (FINE || D >= 2 || TQ == 4) ? 4 : 8;
+  // outputs, two per wave, else all, at most four (64 accumulator registers in FP64)
+  constexpr int NWB = waves(FINE, D), KLMAX = NWB == 8 ? KLMAX_ALL / 2 : KLMAX_ALL;
+  constexpr int PS = FINE ? 2 : (D >= 2 ? 4 : SP), PT = FINE || D >= 2 ? 4 : TQ;
   constexpr int NO = PS * PT / NWB;                       // outputs per wave
   constexpr int PARTS = NOUT / (PS * PT);
   constexpr int NE = PS + PT;                             // entries per column
   constexpr int NX = (NE + NWB - 1) / NWB;                // entries per column copied by a wave
+  constexpr int CW = NE < NWB ? NWB / NE : 1;             // or waves that share one
   constexpr int NM = 1 + D;                               // matrices
   constexpr unsigned MM = (1u << NM) - 1u;
   constexpr int BPE = NM <= 2 ? 2 : 4;                    // plan bits per entry
@@ -151,7 +161,7 @@ __device__ __forceinline__ void tile_numeric() {
   constexpr int PLC = NWB * 64;                           // columns planned at once
   constexpr int SROWS = FINE ? PS * PT : NOUT;            // rows of trace sums kept here
   constexpr int FIXED = KLMAX * 4 + SROWS * NQ * 8 + PLC * 4 + PS * PT * 4 + 128;
-  constexpr int RING = (LDS_BLOCK - FIXED) / 64 * 64;     // bytes of staged blocks
+  constexpr int RING = (160 * 1024 / (16 / NWB) - FIXED) / 64 * 64;     // bytes of staged blocks
   static_assert(RING >= NE * NM * BS * (int)sizeof(T), "a column of 16 x 16 blocks must fit");
   static_assert(!LEARN || RING >= MLP_NP * 4, "the network shares the stage memory");
   __shared__ __attribute__((aligned(16))) char ring[RING + 16];
@@ -551,10 +561,10 @@ __device__ __forceinline__ void tile_numeric() {
           // operand fragments of a staged block: all K-steps at once
           auto frag = [&](int p, T* f) {
             const int q = p + lane * (int)sizeof(T), last = FK ? 3 : ksteps - 1;
-            const int ql = tail ? q + last * 64 * (int)sizeof(T) : RING;
+            const int ql = tail ? q : RING - last * 64 * (int)sizeof(T);
 #pragma unroll
             for (int kk = 0; kk < (FK ? 4 : 3); ++kk)
-              if (kk <= last) f[kk] = *(const T*)(ring + (kk == last ? ql : q + kk * 64 * (int)sizeof(T)));
+              if (kk <= last) f[kk] = *(const T*)(ring + (kk == last ? ql : q) + kk * 64 * (int)sizeof(T));
           };
           Acc<T> tmp[W ? NM : 1];
           if constexpr (W) {
@@ -572,14 +582,17 @@ __device__ __forceinline__ void tile_numeric() {
             }
           };
           // X0's fragments serve all products; those of a direction are read
-          // together, the first direction's before any product
+          // together, the first direction's before any product.  A matrix not
+          // staged is read as well (from a slot behind, unused): between reads
+          // under conditions the compiler waits for the ones before.
           T a0[4], b0[4], xa[4], xb[4];
           auto load_d = [&](int d) {
-            if ((nb >> (1 + d)) & 1u) frag(at(pb, nb, 1 + d), xb);
-            if ((na >> (1 + d)) & 1u) frag(at(pa, na, 1 + d), xa);
+            frag(at(pb, nb, 1 + d), xb);
+            frag(at(pa, na, 1 + d), xa);
+            asm volatile("" ::: "memory");  // here, not moved to the products
           };
-          if (na & 1u) frag(pa, a0);
-          if (nb & 1u) frag(pb, b0);
+          frag(pa, a0);
+          frag(pb, b0);
           if constexpr (D > 0) load_d(0);
           if (na & nb & 1u) prod(dst[0], a0, b0);
 #pragma unroll
@@ -705,7 +718,7 @@ __device__ __forceinline__ void tile_numeric() {
         const unsigned kk = kl[min(c0 + lane, nm - 1)];
 #pragma unroll
         for (int i = 0; i < NX; ++i) {
-          const int x = wave + i * NWB;
+          const int x = CW > 1 ? wave % NE : wave + i * NWB;
           const size_t row = x < PS ? (size_t)(base + (int)(kk >> KLQ_BITS)) * CS + ph + s0 + x
                                     : (size_t)(pq0 + (int)(kk & ((1u << KLQ_BITS) - 1u))) * CS + qh + t0 + min(x - PS, PT - 1);
           at_e[i] = k->panel_e[row];
@@ -723,8 +736,8 @@ __device__ __forceinline__ void tile_numeric() {
         }
 #pragma unroll
         for (int i = 0; i < NX; ++i) {
-          const int x = wave + i * NWB;
-          p.cw[i] = x < NE ? ((first + below(x)) << 4) | ((w >> (BPE * x)) & EM) : 0u;
+          const int x = CW > 1 ? wave % NE : wave + i * NWB;
+          p.cw[i] = x < NE && wave < NE * (CW > 1 ? CW : NX) ? ((first + below(x)) << 4) | ((w >> (BPE * x)) & EM) : 0u;
           p.ce[i] = at_e[i];
           asm volatile("" : "+v"(p.ce[i]));  // loaded before the copies below (the compiler would wait for those too)
         }
@@ -744,10 +757,15 @@ __device__ __forceinline__ void tile_numeric() {
             unsigned n = w & 15u;
             int dst = wrap(((int)(w >> 4) + shift) * sbytes);
             const char* src = (const char*)(X + (size_t)e * PER);
+            int turn = CW > 1 ? wave / NE : 0;
             while (n) {
               const int m = __ffs((int)n) - 1;
               n &= n - 1;
-              lds_copy(src + (size_t)m * BS * sizeof(T), ring_lds + dst, lane * 16, bbytes);
+              if (CW == 1 || turn == 0) {
+                lds_copy(src + (size_t)m * BS * sizeof(T), ring_lds + dst, lane * 16, bbytes);
+                turn = CW;
+              }
+              --turn;
               dst = wrap(dst + sbytes);
             }
           }
@@ -881,15 +899,15 @@ __device__ __forceinline__ void tile_numeric() {
 }
 
 template <typename T, int D, int SP, int TQ, bool BF, bool W, bool FK, int WS>
-__global__ __launch_bounds__(NWB * 64, 4) void k_tile_numeric(TileArgs) {
+__global__ __launch_bounds__(waves(false, D) * 64, 4) void k_tile_numeric(TileArgs) {
   tile_numeric<T, D, SP, TQ, BF, W, FK, WS, false, false>();
 }
 template <typename T, int D, int SP, int TQ, bool BF, bool W, bool FK, int WS>
-__global__ __launch_bounds__(NWB * 64, 4) void k_tile_learn(TileArgs) {
+__global__ __launch_bounds__(waves(false, D) * 64, 4) void k_tile_learn(TileArgs) {
   tile_numeric<T, D, SP, TQ, BF, W, FK, WS, true, false>();
 }
 template <typename T, int D, int SP, int TQ, bool BF, bool W, bool FK, int WS>
-__global__ __launch_bounds__(NWB * 64, 4) void k_tile_fine(TileArgs) {
+__global__ __launch_bounds__(waves(true, D) * 64, 4) void k_tile_fine(TileArgs) {
   tile_numeric<T, D, SP, TQ, BF, W, FK, WS, false, true>();
 }
 
@@ -931,22 +949,22 @@ static unsigned resident_blocks(const void* kernel, int threads) {
 
 template <typename T, int D, int SP, int TQ, bool BF, bool W, bool FK, int WS>
 static void tile_go_w(hipStream_t st, const TileArgs& a) {
-  constexpr int SUBS = (CS / SP) * (CS / TQ), PARTS = SP * TQ / NWB;
+  constexpr int SUBS = (CS / SP) * (CS / TQ), PARTS = SP * TQ / waves(true, D);
   const bool learn = a.skip == 2 || a.log_cap > 0;
   const unsigned subs = (unsigned)a.n_tiles * SUBS;
-  auto go = [&](void (*kernel)(TileArgs), unsigned G) {
+  auto go = [&](void (*kernel)(TileArgs), unsigned G, int threads) {
     if (a.work) {  // persistent: never more blocks than items or than fit at once
-      const unsigned R = resident_blocks((const void*)kernel, NWB * 64);
+      const unsigned R = resident_blocks((const void*)kernel, threads);
       G = G < R ? G : R;
     }
-    hipLaunchKernelGGL(kernel, dim3(G), dim3(NWB * 64), 0, st, a);
+    hipLaunchKernelGGL(kernel, dim3(G), dim3(threads), 0, st, a);
   };
-  if (learn) return go(k_tile_learn<T, D, SP, TQ, BF, W, FK, WS>, subs);
+  if (learn) return go(k_tile_learn<T, D, SP, TQ, BF, W, FK, WS>, subs, waves(false, D) * 64);
   // a.n_tiles bounds the count on the device, where there is one
-  if (subs > (unsigned)a.fine_subs) go(k_tile_numeric<T, D, SP, TQ, BF, W, FK, WS>, subs);
+  if (subs > (unsigned)a.fine_subs) go(k_tile_numeric<T, D, SP, TQ, BF, W, FK, WS>, subs, waves(false, D) * 64);
   if (a.fine_subs > 0 && (subs <= (unsigned)a.fine_subs || a.n_tiles_dev)) {
     const unsigned few = std::min(subs, (unsigned)a.fine_subs);
-    go(k_tile_fine<T, D, SP, TQ, BF, W, FK, WS>, few * PARTS);
+    go(k_tile_fine<T, D, SP, TQ, BF, W, FK, WS>, few * PARTS, waves(true, D) * 64);
     hipLaunchKernelGGL((k_sub_sums<SP * TQ, SUBS>), dim3((few + 15) / 16), dim3(256), 0, st, a,
                        a.waves_per_column == 1 ? SP : SP / WS);
   }
