@@ -72,10 +72,11 @@ __device__ __forceinline__ s4 bf16_frag(const float* tile, int lane) {
 // The same fragment as bf16_frag, each value split into three bfloat16 parts
 // v = h + m + l + r: h = bf16(v), m = bf16(v - h), l = bf16(v - h - m) (the
 // differences are exact in FP32), so that the parts carry 24 significant bits.
-__device__ __forceinline__ void bf16_split3(const float* tile, int lane, s4& h, s4& m, s4& l) {
+__device__ __forceinline__ void bf16_split3(const float* tile, int lane, int b, s4& h, s4& m, s4& l) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const float v = tile[(4 * (lane >> 4) + i) * BP + (lane & 15)];
+    const int c = 4 * (lane >> 4) + i;  // columns from b on are zeros, not stored
+    const float x = tile[c * BP + (lane & 15)], v = c < b ? x : 0.f;
     const __bf16 bh = (__bf16)v;
     const float r1 = v - (float)bh;
     const __bf16 bm = (__bf16)r1;

@@ -301,13 +301,14 @@ bool tile_shape_available(int kind, int D, int shape);
 int tile_shape_default(int kind, int D);
 int tile_subs(int shape);  // sub-tiles per tile of 8 x 8 output blocks
 // Updates of at most this many sub-tiles run in parts of 8 outputs (one per
-// wave), others a sub-tile per workgroup.  512 workgroups fit on the chip: with
-// few sub-tiles the parts fill compute units that would idle or wait for the
-// longest sub-tile (64-atom chain, 72 sub-tiles: 183 -> 70 us per update;
-// 1024-atom chain: 723 -> 520; 100 atoms in three directions, 364: 723 -> 633),
-// with many, operands shared by fewer outputs cost more than the balance gives
-// (343 atoms, 3784 sub-tiles: 5 % slower in parts).
-constexpr int FINE_SUBS = 1024;
+// wave), others a sub-tile per workgroup.  512 workgroups of parts fit on the
+// chip: with few sub-tiles the parts fill compute units that would idle or wait
+// for the longest sub-tile (64-atom chain, 72 sub-tiles: 183 -> 70 us per
+// update; 100 atoms in three directions, 364: 723 -> 633; 1024-atom chain: 24.4
+// ms per solve with a limit of 1024, 23.7 with 2048), with many, operands shared
+// by fewer outputs cost more than the balance gives (343 atoms, 3784 sub-tiles:
+// 6 % slower in parts; batch of five, limit 4096: 8 %).
+constexpr int FINE_SUBS = 2048;
 // bytes of the trace sums per output of those parts
 inline size_t tile_rows_bytes(long long n_tiles) {
   const long long n = n_tiles < 1 ? 1 : n_tiles;

@@ -84,6 +84,18 @@ __device__ __forceinline__ KArgs kargs() {
   return k;
 }
 
+template <typename T>
+__device__ __forceinline__ Acc<T> zero_acc() {
+  Acc<T> c;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) c.v[r] = 0;
+  return c;
+}
+__device__ __forceinline__ void add_wide(AccW& w, const Acc<float>& c) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) w.v[r] += (double)c.v[r];
+}
+
 // inclusive sum over the lanes of a wave (six data-parallel adds)
 __device__ __forceinline__ int wave_scan(int v) {
   v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
@@ -131,6 +143,10 @@ __device__ __forceinline__ double sub_sum(const double* row, int ng, int go) {
 // outputs, group (h, v) holding (I_s, J_{(s+v) mod TQ}) for the rows s of part
 // h, first within a group, then over the groups: a fixed order, whichever
 // wave computed which output.
+// A bfloat16 split is made once per staged block, by the wave that copied it, in
+// place: h, m and l of the values of lane l's fragment at 8 l in three planes of
+// 512 B (split at each of its 4 uses instead: 343 atoms in three directions, two
+// thirds of the time in this kind, 134 ms per solve against 128).
 // LEARN: with the skip network or feature logging (kept apart, as its code
 // would take registers from the products).
 template <typename T, int D, int SP, int TQ, bool BF, bool W, bool FK, int WS, bool LEARN, bool FINE>
@@ -162,7 +178,7 @@ __device__ __forceinline__ void tile_numeric() {
   constexpr int SROWS = FINE ? PS * PT : NOUT;            // rows of trace sums kept here
   constexpr int FIXED = KLMAX * 4 + SROWS * NQ * 8 + PLC * 4 + PS * PT * 4 + 128;
   constexpr int RING = (160 * 1024 / (16 / NWB) - FIXED) / 64 * 64;     // bytes of staged blocks
-  static_assert(RING >= NE * NM * BS * (int)sizeof(T), "a column of 16 x 16 blocks must fit");
+  static_assert(RING >= NE * NM * BS * (BF && W ? 6 : (int)sizeof(T)), "a column of 16 x 16 blocks must fit");
   static_assert(!LEARN || RING >= MLP_NP * 4, "the network shares the stage memory");
   __shared__ __attribute__((aligned(16))) char ring[RING + 16];
   __shared__ unsigned kl[KLMAX];
@@ -176,8 +192,9 @@ __device__ __forceinline__ void tile_numeric() {
   constexpr int NT = NWB * 64;
   const T* X = (const T*)k->xv;
   const int b = k->b, ksteps = k->ksteps;
-  const int bbytes = ((LEARN && BF) ? BP : b) * BP * (int)sizeof(T);  // copied of a block
-  const int sbytes = (BF ? BP : b) * BP * (int)sizeof(T);  // a slot
+  constexpr bool SPLIT = BF && W;
+  const int bbytes = ((LEARN && BF && !W) ? BP : b) * BP * (int)sizeof(T);  // copied of a block
+  const int sbytes = SPLIT ? 3 * BS * 2 : (BF ? BP : b) * BP * (int)sizeof(T);  // a slot
   const int nslot = RING / sbytes;                        // blocks the ring holds
   const int rbytes = nslot * sbytes;
   const unsigned ring_lds = (unsigned)(unsigned long long)(lds_void*)ring;  // its LDS offset
@@ -498,51 +515,49 @@ __device__ __forceinline__ void tile_numeric() {
         auto at = [&](int p, unsigned n, int m) { return wrap(p + __popc(n & ((1u << m) - 1u)) * sbytes); };
         nprod += __popc(na & nb & 1u) + ((na & 1u) ? __popc(nb >> 1) : 0) + ((nb & 1u) ? __popc(na >> 1) : 0);
         if constexpr (BF) {
-          Acc<float> tmp[W ? NM : 1];
-          if constexpr (W) {
-#pragma unroll
-            for (int m = 0; m < NM; ++m)
-#pragma unroll
-              for (int r = 0; r < 4; ++r) tmp[m].v[r] = 0.f;
-          }
           if constexpr (W) {
             // bfloat16 three-way split: each operand value v = h + m + l; the six
             // cross products above 2^-24 of the leading term (l h, h l, m m, m h,
             // h m, h h, smallest first) run as 16x16x16 bfloat16 MFMAs into an
             // FP32 temporary per column block, which is added to the FP64 sums
-            s4 a0[3], b0[3], x1[3];
-            auto prod3 = [&](Acc<float>& c, const s4* u, const s4* v) {
-              mfma_bf16(c, u[2], v[0]);
-              mfma_bf16(c, u[0], v[2]);
-              mfma_bf16(c, u[1], v[1]);
-              mfma_bf16(c, u[1], v[0]);
-              mfma_bf16(c, u[0], v[1]);
-              mfma_bf16(c, u[0], v[0]);
+            struct Part {
+              s4 v[3];
             };
-            if (na & 1u) bf16_split3((const float*)(ring + pa), lane, a0[0], a0[1], a0[2]);
-            if (nb & 1u) bf16_split3((const float*)(ring + pb), lane, b0[0], b0[1], b0[2]);
-            if (na & nb & 1u) prod3(tmp[0], a0, b0);
+            auto part = [&](int p) {
+              Part f;
+#pragma unroll
+              for (int k = 0; k < 3; ++k) f.v[k] = *(const s4*)(ring + p + k * 512 + lane * 8);
+              return f;
+            };
+            auto prod3 = [&](Acc<float>& c, const Part& u, const Part& v) {
+              mfma_bf16(c, u.v[2], v.v[0]);
+              mfma_bf16(c, u.v[0], v.v[2]);
+              mfma_bf16(c, u.v[1], v.v[1]);
+              mfma_bf16(c, u.v[1], v.v[0]);
+              mfma_bf16(c, u.v[0], v.v[1]);
+              mfma_bf16(c, u.v[0], v.v[0]);
+            };
+            const Part a0 = part(pa), b0 = part(pb);
+            if (na & nb & 1u) {
+              Acc<float> tmp = zero_acc<float>();
+              prod3(tmp, a0, b0);
+              add_wide(wacc[o][0], tmp);
+            }
 #pragma unroll
             for (int d = 0; d < D; ++d) {
-              if (na & (nb >> (1 + d)) & 1u) {
-                bf16_split3((const float*)(ring + at(pb, nb, 1 + d)), lane, x1[0], x1[1], x1[2]);
-                prod3(tmp[1 + d], a0, x1);
+              const Part xb = part(at(pb, nb, 1 + d)), xa = part(at(pa, na, 1 + d));
+              asm volatile("" ::: "memory");  // read here, not moved to the products
+              const bool p0 = na & (nb >> (1 + d)) & 1u, p1 = (na >> (1 + d)) & nb & 1u;
+              if (!(p0 || p1)) continue;
+              Acc<float> tmp = zero_acc<float>();
+              if (p0) {
+                prod3(tmp, a0, xb);
+                if (p1) prod3(tmp, xa, b0);
+              } else {
+                prod3(tmp, xa, b0);
               }
-              if ((na >> (1 + d)) & nb & 1u) {
-                bf16_split3((const float*)(ring + at(pa, na, 1 + d)), lane, x1[0], x1[1], x1[2]);
-                prod3(tmp[1 + d], x1, b0);
-              }
+              add_wide(wacc[o][1 + d], tmp);
             }
-            if (na & nb & 1u) {
-#pragma unroll
-              for (int r = 0; r < 4; ++r) wacc[o][0].v[r] += (double)tmp[0].v[r];
-            }
-#pragma unroll
-            for (int d = 0; d < D; ++d)
-              if (((na & (nb >> (1 + d))) | ((na >> (1 + d)) & nb)) & 1u) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) wacc[o][1 + d].v[r] += (double)tmp[1 + d].v[r];
-              }
           } else {
             // bfloat16 operands: one 16x16x16 MFMA per block product
             s4 a0, b0;
@@ -743,9 +758,10 @@ __device__ __forceinline__ void tile_numeric() {
         }
       };
 
-      // copy the needed blocks of the columns [c0, c1) of plan p into the ring,
-      // block n of the chunk to slot n + shift (modulo the ring)
-      auto copy = [&](const Plan& p, int c0, int c1, int shift) {
+      // f(slot offset, matrix, entry) for the blocks that this wave copies of the
+      // columns [c0, c1) of plan p, block n of the chunk in slot n + shift
+      // (modulo the ring)
+      auto each_block = [&](const Plan& p, int c0, int c1, int shift, auto&& f) {
 #pragma unroll
         for (int i = 0; i < NX; ++i) {
           unsigned long long todo = __ballot(lane >= c0 && lane < c1 && (p.cw[i] & 15u));
@@ -756,13 +772,12 @@ __device__ __forceinline__ void tile_numeric() {
             const unsigned w = (unsigned)__builtin_amdgcn_readlane((int)p.cw[i], l);
             unsigned n = w & 15u;
             int dst = wrap(((int)(w >> 4) + shift) * sbytes);
-            const char* src = (const char*)(X + (size_t)e * PER);
             int turn = CW > 1 ? wave / NE : 0;
             while (n) {
               const int m = __ffs((int)n) - 1;
               n &= n - 1;
               if (CW == 1 || turn == 0) {
-                lds_copy(src + (size_t)m * BS * sizeof(T), ring_lds + dst, lane * 16, bbytes);
+                f(dst, m, e);
                 turn = CW;
               }
               --turn;
@@ -770,6 +785,23 @@ __device__ __forceinline__ void tile_numeric() {
             }
           }
         }
+      };
+      auto copy = [&](const Plan& p, int c0, int c1, int shift) {
+        each_block(p, c0, c1, shift, [&](int dst, int m, int e) {
+          lds_copy((const char*)(X + (size_t)e * PER + (size_t)m * BS), ring_lds + dst, lane * 16, bbytes);
+        });
+      };
+      // split the blocks that copy() with the same arguments has put in place
+      auto split_own = [&](const Plan& p, int c0, int c1, int shift) {
+        each_block(p, c0, c1, shift, [&](int dst, int, int) {
+          s4 h, m, l;
+          bf16_split3((const float*)(ring + dst), lane, b, h, m, l);
+          s4* out = (s4*)(ring + dst) + lane;
+          asm volatile("" ::: "memory");  // the block is in registers
+          out[0] = h;
+          out[64] = m;
+          out[128] = l;
+        });
       };
 
       for (int base = pp0; base < pp1; base += KLC) {
@@ -827,6 +859,7 @@ __device__ __forceinline__ void tile_numeric() {
           usize = vsize;
           const int ushift = vshift;
           asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+          if constexpr (SPLIT) split_own(nxt, u0, u1, ushift);
           __syncthreads();
           more = stage_next();
 #pragma unroll
