@@ -17,18 +17,25 @@ namespace tc2 {
 
 // ------------------------------------------------------------------ Gershgorin
 // Bounds of the spectrum of H (Sec. 2.2): per scalar row i, H_ii -+ sum_{j!=i} |H_ij|.
-__global__ void k_gershgorin(int nb, int b, const int* rp, const int* ci, const double* hv,
-                             double* rowlo, double* rowhi) {
+// One thread per scalar row, its sums in the order of the entries and columns;
+// the padded columns are zeros, so that the 16 of a block are read at once
+// (125 atoms, dense: 585 us with a load at a time, 54 now).
+__global__ __launch_bounds__(64) void k_gershgorin(int nb, int b, const int* rp, const int* ci,
+                                                   const double* hv, double* rowlo, double* rowhi) {
   int g = blockIdx.x * blockDim.x + threadIdx.x;
   if (g >= nb * b) return;
   int I = g / b, r = g - I * b;
   double sum = 0.0, centre = 0.0;
+#pragma unroll 2
   for (int e = rp[I]; e < rp[I + 1]; ++e) {
     const double* blk = hv + (size_t)e * BS;
     bool diag = ci[e] == I;
-    for (int c = 0; c < b; ++c) {
-      double v = blk[c * BP + r];
-      if (diag && c == r) centre = v; else sum += fabs(v);
+    double v[BP];
+#pragma unroll
+    for (int c = 0; c < BP; ++c) v[c] = blk[c * BP + r];
+#pragma unroll
+    for (int c = 0; c < BP; ++c) {
+      if (diag && c == r) centre = v[c]; else sum += fabs(v[c]);
     }
   }
   rowlo[g] = centre - sum;
@@ -329,59 +336,84 @@ __global__ __launch_bounds__(256) void k_numeric(NumArgs a) {
 
 // ------------------------------------------------------------------ measure
 // Scalars of the current iterate (Tr X0, ||X0||_F^2, band energies, alpha)
-// straight from its stored blocks; used for the initial matrices.  One wave
-// per row, entries J >= I weighted by 2 off the diagonal.
+// straight from its stored blocks; used for the initial and final matrices.  One
+// block per row, entries J >= I weighted by 2 off the diagonal: a wave takes an
+// entry, and the row's sums are taken over its entries in order.  Bound by the
+// latency of the loads: with one wave per row, and the entry of H found by a
+// serial walk over H's row, 653 us for 125 atoms (dense), now 55.
+constexpr int MEAS_W = 8;    // waves of a block
+constexpr int MEAS_E = 64;   // entries between two sums
+
+// first of the entries [f, end) with column J, or -1 (called by a whole wave)
+__device__ __forceinline__ int find_column(const int* ci, int f, int end, int J) {
+  const int lane = threadIdx.x & 63;
+  for (; f < end; f += 64) {
+    const unsigned long long m = __ballot(f + lane < end && ci[f + lane] == J);
+    if (m) return f + __ffsll((long long)m) - 1;
+  }
+  return -1;
+}
+
 template <typename T, int D>
-__global__ __launch_bounds__(64) void k_measure(MeasArgs a) {
-  const int I = blockIdx.x;
-  const int lane = threadIdx.x;
+__global__ __launch_bounds__(MEAS_W * 64) void k_measure(MeasArgs a) {
+  __shared__ double terms[MEAS_E][NQ];
+  const int I = blockIdx.x, t = threadIdx.x;
+  const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const T* X = (const T*)a.xv;
   const size_t stride = (size_t)(1 + D) * BS;
-  double q[NQ];
+  const int end = a.rp[I + 1];
+  double sum = 0.0;
+  for (int base = a.rp[I]; base < end; base += MEAS_E) {
+    const int n = min(MEAS_E, end - base);
+    for (int i = wave; i < n; i += MEAS_W) {
+      const int e = base + i, J = a.ci[e];
+      double q[NQ];
 #pragma unroll
-  for (int k = 0; k < NQ; ++k) q[k] = 0.0;
-  for (int e = a.rp[I]; e < a.rp[I + 1]; ++e) {
-    const int J = a.ci[e];
-    if (J < I) continue;
-    const double w = (J == I) ? 1.0 : 2.0;
-    int eh = -1;
-    for (int f = a.h_rp[I]; f < a.h_rp[I + 1]; ++f)
-      if (a.h_ci[f] == J) { eh = f; break; }
-    for (int m = 0; m <= D; ++m) {
-      double tr = 0.0, ss = 0.0, dh = 0.0, d1 = 0.0;
-      int e1 = -1;
-      if (m > 0)
-        for (int f = a.h1_rp[m - 1][I]; f < a.h1_rp[m - 1][I + 1]; ++f)
-          if (a.h1_ci[m - 1][f] == J) { e1 = f; break; }
-      for (int j = 0; j < 4; ++j) {
-        const int qd = lane + 64 * j;
-        const double x = (double)X[(size_t)e * stride + m * BS + qd];
-        if (J == I && (qd & 15) == (qd >> 4)) tr += x;
-        ss += x * x;
-        if (eh >= 0) dh += x * a.h_v[(size_t)eh * BS + qd];
-        if (e1 >= 0) d1 += x * a.h1_v[m - 1][(size_t)e1 * BS + qd];
+      for (int k = 0; k < NQ; ++k) q[k] = 0.0;
+      if (J >= I) {
+        const double w = (J == I) ? 1.0 : 2.0;
+        const int eh = find_column(a.h_ci, a.h_rp[I], a.h_rp[I + 1], J);
+#pragma unroll
+        for (int m = 0; m <= D; ++m) {
+          double tr = 0.0, ss = 0.0, dh = 0.0, d1 = 0.0;
+          int e1 = -1;
+          if (m > 0)
+            e1 = find_column(a.h1_ci[m - 1], a.h1_rp[m - 1][I], a.h1_rp[m - 1][I + 1], J);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int qd = lane + 64 * j;
+            const double x = (double)X[(size_t)e * stride + m * BS + qd];
+            if (J == I && (qd & 15) == (qd >> 4)) tr += x;
+            ss += x * x;
+            if (eh >= 0) dh += x * a.h_v[(size_t)eh * BS + qd];
+            if (e1 >= 0) d1 += x * a.h1_v[m - 1][(size_t)e1 * BS + qd];
+          }
+          tr = wave_sum(tr);
+          ss = wave_sum(ss);
+          dh = wave_sum(dh);
+          if (m == 0) {
+            q[Q_TR0] = tr;
+            q[Q_FRO0] = w * ss;
+            q[Q_E0] = w * dh;
+          } else {
+            d1 = wave_sum(d1);
+            q[Q_TR1 + m - 1] = tr;
+            q[Q_E1 + m - 1] = w * dh;
+            q[Q_AL + m - 1] = w * d1;
+          }
+        }
       }
-      tr = wave_sum(tr);
-      ss = wave_sum(ss);
-      dh = wave_sum(dh);
-      d1 = wave_sum(d1);
-      if (m == 0) {
-        q[Q_TR0] += tr;
-        q[Q_FRO0] += w * ss;
-        q[Q_E0] += w * dh;
-      } else {
-        q[Q_TR1 + m - 1] += tr;
-        q[Q_E1 + m - 1] += w * dh;
-        q[Q_AL + m - 1] += w * d1;
-      }
+      double out = 0.0;
+#pragma unroll
+      for (int k = 0; k < NQ; ++k) out = (lane == k) ? q[k] : out;
+      if (lane < NQ) terms[i][lane] = out;
     }
+    __syncthreads();
+    if (t < NQ)
+      for (int i = 0; i < n; ++i) sum += terms[i][t];
+    __syncthreads();
   }
-  if (lane < NQ) {
-    double out = 0.0;
-#pragma unroll
-    for (int k = 0; k < NQ; ++k) out = (lane == k) ? q[k] : out;
-    a.partial[(size_t)I * NQ + lane] = out;
-  }
+  if (t < NQ) a.partial[(size_t)I * NQ + t] = sum;
 }
 
 // ------------------------------------------------------------------ compaction
@@ -565,7 +597,7 @@ void launch_gershgorin(hipStream_t st, int nb, int b, const int* rp, const int* 
                        const double* hv, double* rowlo, double* rowhi) {
   long long n = (long long)nb * b;
   if (n == 0) return;
-  hipLaunchKernelGGL(k_gershgorin, dim3(nblk(n, 256)), dim3(256), 0, st, nb, b, rp, ci, hv,
+  hipLaunchKernelGGL(k_gershgorin, dim3(nblk(n, 64)), dim3(64), 0, st, nb, b, rp, ci, hv,
                      rowlo, rowhi);
 }
 
@@ -643,10 +675,10 @@ void launch_numeric(hipStream_t st, int prec, const NumArgs& a) {
 template <typename T>
 static void measure_d(hipStream_t st, const MeasArgs& a) {
   switch (a.D) {
-    case 0: hipLaunchKernelGGL((k_measure<T, 0>), dim3(a.nb), dim3(64), 0, st, a); break;
-    case 1: hipLaunchKernelGGL((k_measure<T, 1>), dim3(a.nb), dim3(64), 0, st, a); break;
-    case 2: hipLaunchKernelGGL((k_measure<T, 2>), dim3(a.nb), dim3(64), 0, st, a); break;
-    default: hipLaunchKernelGGL((k_measure<T, 3>), dim3(a.nb), dim3(64), 0, st, a); break;
+    case 0: hipLaunchKernelGGL((k_measure<T, 0>), dim3(a.nb), dim3(MEAS_W * 64), 0, st, a); break;
+    case 1: hipLaunchKernelGGL((k_measure<T, 1>), dim3(a.nb), dim3(MEAS_W * 64), 0, st, a); break;
+    case 2: hipLaunchKernelGGL((k_measure<T, 2>), dim3(a.nb), dim3(MEAS_W * 64), 0, st, a); break;
+    default: hipLaunchKernelGGL((k_measure<T, 3>), dim3(a.nb), dim3(MEAS_W * 64), 0, st, a); break;
   }
 }
 
