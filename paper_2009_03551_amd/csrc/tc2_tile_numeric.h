@@ -29,7 +29,7 @@ namespace tc2 {
 //
 // Measured (MI355X).  Reading the operands from global memory instead (no LDS,
 // no barrier) is bound by the fabric behind L2 (9.7 TB/s of operands): 877 ms
-// per solve of a 1728-atom lattice in three directions, against 677 here; the
+// per solve of a 1728-atom lattice in three directions, against 675 here; the
 // kernel before, a column and two barriers at a time in blocks of 16 x 16 with
 // every matrix of a present block staged, took 1001.  What remains: an FP64 or
 // FP32 MFMA leaves no issue slot to the vector ALU of its SIMD (measured with
@@ -38,7 +38,7 @@ namespace tc2 {
 // of a stage for its busiest wave (1.5 times the mean) and for copies of columns
 // too large to stand in the ring beside the stage in use.  Hence the packed
 // plan words, scalar addresses and arguments read where they are used, and
-// fragments read without conditions, four to eight reads in flight (with
+// fragments read without conditions while the products before run (with
 // conditions the compiler waited at each: 688 ms, and 346 instead of 333 for
 // 1000 atoms in one direction).
 // Sub-tiles dealt to the XCDs in chunks (L2 hits 10 -> 17 %) and half the blocks
@@ -597,26 +597,27 @@ __device__ __forceinline__ void tile_numeric() {
             }
           };
           // X0's fragments serve all products; those of a direction are read
-          // together, the first direction's before any product.  A matrix not
-          // staged is read as well (from a slot behind, unused): between reads
-          // under conditions the compiler waits for the ones before.
+          // while the products before run.  A matrix not staged is read as well
+          // (from a slot behind, unused): between reads under conditions the
+          // compiler waits for the ones before.
           T a0[4], b0[4], xa[4], xb[4];
-          auto load_d = [&](int d) {
-            frag(at(pb, nb, 1 + d), xb);
-            frag(at(pa, na, 1 + d), xa);
+          auto load = [&](int p, T* f) {
+            frag(p, f);
             asm volatile("" ::: "memory");  // here, not moved to the products
           };
-          frag(pa, a0);
-          frag(pb, b0);
-          if constexpr (D > 0) load_d(0);
+          load(pa, a0);
+          load(pb, b0);
+          if constexpr (D > 0) {
+            load(at(pb, nb, 1), xb);
+            load(at(pa, na, 1), xa);
+          }
           if (na & nb & 1u) prod(dst[0], a0, b0);
 #pragma unroll
           for (int d = 0; d < D; ++d) {
-            if (d > 0) load_d(d);
             if (na & (nb >> (1 + d)) & 1u) prod(dst[1 + d], a0, xb);
-            if ((na >> (1 + d)) & nb & 1u) {
-              prod(dst[1 + d], xa, b0);
-            }
+            if (d + 1 < D) load(at(pb, nb, 2 + d), xb);
+            if ((na >> (1 + d)) & nb & 1u) prod(dst[1 + d], xa, b0);
+            if (d + 1 < D) load(at(pa, na, 2 + d), xa);
           }
           if constexpr (W) {
             if (na & nb & 1u) {
