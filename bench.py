@@ -46,7 +46,7 @@ def kernel_name(kernel: str, kind: int, D: int, shape: int, b: int, split: bool 
     sp, tq = SHAPES[max(shape, 0)]
     bf = kind == 2 or (split and kind == 3)
     full_k = b > 12 and not bf
-    # waves per sub-tile column: four for the 4 x 4 sub-tile with D >= 2 (FP64,
+    # groups of trace sums per sub-tile column: four for the 4 x 4 sub-tile with D >= 2 (FP64,
     # and the kinds with FP64 sums), two for the 8 x 8 sub-tile with D <= 1
     # (FP64, FP32 with FP64 sums)
     ws = 1

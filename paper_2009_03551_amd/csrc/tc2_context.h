@@ -313,7 +313,7 @@ struct tc2_ctx {
   int test_fine_subs = tc2::FINE_SUBS;  // fewer: sub-tiles not split into parts
   long long test_stage_cap = 0;
   int test_no_zero_skip = 0;      // issue every product (masks not passed to the kernel)
-  int test_waves_per_column = 0;  // 1: one wave per sub-tile column in every numeric kernel
+  int test_waves_per_column = 0;  // 1: trace sums grouped by sub-tile column in every numeric kernel
   std::vector<int> h_active;      // host copy of the active flags
   // clusters
   int nc = 0, max_sys_clusters = 0;

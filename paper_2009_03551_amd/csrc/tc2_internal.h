@@ -182,7 +182,7 @@ struct TileArgs {
   int kl_chunk;           // 0: default panel pass length
   int b;                  // block size
   int ksteps;             // ceil(b / 4): K-steps of 4 in the padded tile
-  int waves_per_column;   // 1: one wave per column of the 4 x 4 sub-tile (tests compare)
+  int waves_per_column;   // 1: trace sums grouped by column of the sub-tile only (tests compare)
   int n_tiles;
   const int* rp;
   const int* ci;

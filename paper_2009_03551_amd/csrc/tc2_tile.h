@@ -5,7 +5,7 @@
 
 namespace tc2 {
 
-// Sub-tile shapes (rows of cluster P x columns of cluster Q per workgroup).
+// Sub-tile shapes (rows of cluster P x columns of cluster Q per work item).
 // Which ones exist depends on the kernel kind and D: the accumulators of a
 // wave ((1 + D) tiles per owned output) must stay within its register budget.
 constexpr int SHAPE_SP[TS_N] = {8, 4, 8, 4};

@@ -1,14 +1,13 @@
-// Clustered-tile numeric kernel of the TC2 / TC2-CPSCF update for gfx950.
+// Cluster panels and tiles of the TC2 / TC2-CPSCF update for gfx950, the
+// copy-through of stopped systems, block norms, and the choice among the
+// instances of the clustered-tile numeric kernel (tc2_tile_numeric.h).
 //
-// Atoms are grouped into clusters of up to CS = 8 nearby atoms.  A work item
-// is a tile of output blocks (I in cluster P) x (J in cluster Q) for P <= Q;
-// it walks the common columns K of the two clusters' row panels once and, for
-// every K, stages the present blocks X_JK of cluster Q in LDS while each wave
-// holds the MFMA fragments of its X_IK in registers.  Every staged block then
-// feeds up to 8 block products instead of one, which cuts the L2/HBM operand
-// traffic of the row-by-row product (Algorithm 1) several-fold.  The
-// accumulators and the fused epilogue (branch combine, Frobenius drop,
-// traces and band energies) are the same as in the one-wave-per-block kernel.
+// Atoms are grouped into clusters of up to CS = 8 nearby atoms.  A tile holds
+// the output blocks (I in cluster P) x (J in cluster Q) for P <= Q; its
+// products walk the common columns of the two clusters' row panels, so that an
+// operand block staged in LDS feeds up to 8 block products instead of one,
+// which cuts the L2/HBM operand traffic of the row-by-row product
+// (Algorithm 1) several-fold.
 #include "tc2_device.h"
 #include "tc2_tile.h"
 
