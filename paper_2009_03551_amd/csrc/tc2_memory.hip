@@ -332,8 +332,10 @@ hipError_t vm_grow(DBuf& b, size_t n) {
   return hipSuccess;
 }
 
-// Unmap every chunk of b (once the device is idle) into the pool, and free
-// its virtual range.
+// Unmap the chunks of b (once the device is idle) into the pool.  Its range is
+// freed, or kept with the first chunk mapped; what stands in the pool may be
+// another thread's at once, so the range goes there after its other chunks are
+// unmapped.
 void vm_release(DBuf& b) {
   if (!b.vm) return;
   int cur = 0;
@@ -341,20 +343,23 @@ void vm_release(DBuf& b) {
   if (cur != b.dev) (void)hipSetDevice(b.dev);
   (void)hipDeviceSynchronize();
   Pool& P = g_pool[b.dev];
+  for (size_t k = 1; k < b.chunks.size(); ++k) (void)hipMemUnmap((char*)b.p + k * P.chunk, P.chunk);
   bool kept = false;
-  if (b.chunks.size() >= 1) {
+  if (!b.chunks.empty()) {
     std::lock_guard<std::mutex> g(P.m);
+    P.free.insert(P.free.end(), b.chunks.begin() + 1, b.chunks.end());
     kept = P.ranges.size() < RANGES;
     if (kept) P.ranges.emplace_back(b.p, b.chunks[0]);  // within the capacity reserved in pool_of
   }
-  for (size_t k = kept ? 1 : 0; k < b.chunks.size(); ++k)
-    (void)hipMemUnmap((char*)b.p + k * P.chunk, P.chunk);
-  {
-    std::lock_guard<std::mutex> g(P.m);
-    P.free.insert(P.free.end(), b.chunks.begin() + (kept ? 1 : 0), b.chunks.end());
+  if (!kept) {
+    if (!b.chunks.empty()) {
+      (void)hipMemUnmap(b.p, P.chunk);
+      std::lock_guard<std::mutex> g(P.m);
+      P.free.push_back(b.chunks[0]);
+    }
+    (void)hipMemAddressFree(b.p, b.va);
   }
   b.chunks.clear();
-  if (!kept) (void)hipMemAddressFree(b.p, b.va);
   if (cur != b.dev) (void)hipSetDevice(cur);
   b.p = nullptr;
   b.cap = 0;

@@ -1,0 +1,207 @@
+// The buffer pool of the library (tc2_memory.hip) as a host program over a
+// model of the device's memory: which allocations exist, and which chunk is
+// mapped at which address of a reserved range.  The model aborts the program
+// with a message on a call that the driver would refuse or that would take
+// memory away from a buffer in use.  One scenario per run, named by argv[1].
+#include "../../paper_2009_03551_amd/csrc/tc2_memory.hip"
+
+#include <stdio.h>
+#include <string.h>
+
+#include <atomic>
+#include <chrono>
+#include <functional>
+#include <set>
+#include <thread>
+
+namespace {
+
+constexpr size_t MB = (size_t)1 << 20, GB = (size_t)1 << 30;
+
+[[noreturn]] void fail(const char* what) {
+  fprintf(stderr, "FAILED: %s\n", what);
+  fflush(stderr);
+  _Exit(1);
+}
+void check(bool ok, const char* what) {
+  if (!ok) fail(what);
+}
+
+std::mutex g_m;
+uintptr_t g_next = GB;                       // next address handed out
+size_t g_capacity = 64 * GB, g_in_use = 0;   // device memory
+std::map<uintptr_t, size_t> g_alloc;         // plain allocations
+std::map<uintptr_t, size_t> g_reserved;      // virtual ranges
+std::map<uintptr_t, uint64_t> g_mapped;      // address -> chunk
+std::map<uint64_t, size_t> g_chunk;          // chunk -> bytes
+uint64_t g_next_chunk = 1;
+std::atomic<int> g_stream_waits{0}, g_device_waits{0};
+std::function<void(void*)> g_on_unmap;       // before a mapping is taken away
+
+// calls of every kind that the pool makes, in the model
+bool chunk_mapped(uint64_t h) {
+  for (auto& m : g_mapped)
+    if (m.second == h) return true;
+  return false;
+}
+
+}  // namespace
+
+extern "C" {
+
+hipError_t hipGetDevice(int* d) { return *d = 0, hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipDeviceSynchronize() { return ++g_device_waits, hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return ++g_stream_waits, hipSuccess; }
+hipError_t hipDeviceTotalMem(size_t* n, hipDevice_t) { return *n = g_capacity, hipSuccess; }
+
+hipError_t hipMalloc(void** p, size_t n) {
+  std::lock_guard<std::mutex> g(g_m);
+  if (g_in_use + n > g_capacity) return hipErrorOutOfMemory;
+  g_in_use += n;
+  g_alloc[g_next] = n;
+  *p = (void*)g_next;
+  g_next += (n + MB) / MB * MB;
+  return hipSuccess;
+}
+hipError_t hipFree(void* p) {
+  std::lock_guard<std::mutex> g(g_m);
+  auto it = g_alloc.find((uintptr_t)p);
+  check(it != g_alloc.end(), "hipFree of an address that is not allocated");
+  g_in_use -= it->second;
+  g_alloc.erase(it);
+  return hipSuccess;
+}
+hipError_t hipMemGetAllocationGranularity(size_t* g, const hipMemAllocationProp*,
+                                          hipMemAllocationGranularity_flags) {
+  return *g = 2 * MB, hipSuccess;
+}
+hipError_t hipMemAddressReserve(void** p, size_t n, size_t, void*, unsigned long long) {
+  std::lock_guard<std::mutex> g(g_m);
+  g_reserved[g_next] = n;
+  *p = (void*)g_next;
+  g_next += n;
+  return hipSuccess;
+}
+hipError_t hipMemAddressFree(void* p, size_t n) {
+  std::lock_guard<std::mutex> g(g_m);
+  auto it = g_reserved.find((uintptr_t)p);
+  check(it != g_reserved.end() && it->second == n, "a range freed that is not reserved");
+  for (auto& m : g_mapped)
+    check(m.first < it->first || m.first >= it->first + n, "a range freed with a chunk mapped in it");
+  g_reserved.erase(it);
+  return hipSuccess;
+}
+hipError_t hipMemCreate(hipMemGenericAllocationHandle_t* h, size_t n, const hipMemAllocationProp*,
+                        unsigned long long) {
+  std::lock_guard<std::mutex> g(g_m);
+  if (g_in_use + n > g_capacity) return hipErrorOutOfMemory;
+  g_in_use += n;
+  g_chunk[g_next_chunk] = n;
+  *h = (hipMemGenericAllocationHandle_t)g_next_chunk++;
+  return hipSuccess;
+}
+hipError_t hipMemRelease(hipMemGenericAllocationHandle_t h) {
+  std::lock_guard<std::mutex> g(g_m);
+  auto it = g_chunk.find((uint64_t)h);
+  check(it != g_chunk.end(), "a chunk released twice");
+  check(!chunk_mapped(it->first), "a chunk released while it is mapped");
+  g_in_use -= it->second;
+  g_chunk.erase(it);
+  return hipSuccess;
+}
+hipError_t hipMemMap(void* p, size_t, size_t, hipMemGenericAllocationHandle_t h, unsigned long long) {
+  std::lock_guard<std::mutex> g(g_m);
+  check(!g_mapped.count((uintptr_t)p), "a chunk mapped where another one still is");
+  check(!chunk_mapped((uint64_t)h), "a chunk mapped twice");
+  g_mapped[(uintptr_t)p] = (uint64_t)h;
+  return hipSuccess;
+}
+hipError_t hipMemUnmap(void* p, size_t) {
+  if (g_on_unmap) g_on_unmap(p);
+  std::lock_guard<std::mutex> g(g_m);
+  check(g_mapped.erase((uintptr_t)p) == 1, "unmapped where nothing is mapped");
+  return hipSuccess;
+}
+hipError_t hipMemSetAccess(void*, size_t, const hipMemAccessDesc*, size_t) { return hipSuccess; }
+
+}  // extern "C"
+
+namespace {
+
+using namespace tc2;
+
+// every chunk of b is mapped where b takes it to be
+void whole(const DBuf& b, const char* what) {
+  std::lock_guard<std::mutex> g(g_m);
+  for (size_t k = 0; k < b.chunks.size(); ++k) {
+    auto it = g_mapped.find((uintptr_t)b.p + k * 256 * MB);
+    check(it != g_mapped.end() && it->second == (uint64_t)b.chunks[k], what);
+  }
+}
+
+// One buffer is released, and while its chunks are being unmapped another
+// thread grows a buffer of its own.
+void release_beside_grow() {
+  DBuf first, second;
+  check(first.reserve(900 * MB) == hipSuccess, "first buffer");
+  std::thread other;
+  std::atomic<bool> done{false};
+  g_on_unmap = [&](void*) {
+    if (other.joinable()) return;
+    other = std::thread([&] {
+      check(second.reserve(1100 * MB) == hipSuccess, "second buffer");
+      whole(second, "a chunk of the second buffer is not where it was mapped");
+      done = true;
+    });
+    // it may have to wait for a lock of the release: no longer than this
+    for (int i = 0; i < 200 && !done; ++i) std::this_thread::sleep_for(std::chrono::milliseconds(1));
+  };
+  first.release();
+  check(other.joinable(), "the release unmapped nothing");
+  other.join();
+  g_on_unmap = nullptr;
+  check(second.chunks.size() == 5, "size of the second buffer");
+  whole(second, "a chunk of the second buffer was taken away");
+  // what the release gave back serves the next buffers
+  DBuf third;
+  check(third.reserve(700 * MB) == hipSuccess, "third buffer");
+  whole(third, "third buffer");
+  second.release();
+  third.release();
+  pool_trim();
+  check(g_in_use == 0 && g_mapped.empty() && g_reserved.empty(), "memory left after the trim");
+}
+
+// Several threads growing and releasing buffers of 1 to 5 chunks.
+void many_threads() {
+  std::vector<std::thread> ts;
+  for (int t = 0; t < 6; ++t)
+    ts.emplace_back([t] {
+      unsigned s = 12345u * (unsigned)(t + 1);
+      for (int k = 0; k < 400; ++k) {
+        s = s * 1664525u + 1013904223u;
+        DBuf b;
+        check(b.reserve((100 + (s >> 8) % 1100) * MB) == hipSuccess, "reserve");
+        whole(b, "a chunk is not where it was mapped");
+        std::this_thread::yield();
+        whole(b, "a chunk was taken away");
+        if (k % 50 == 49) pool_trim();
+      }
+    });
+  for (std::thread& t : ts) t.join();
+  pool_trim();
+  check(g_in_use == 0 && g_mapped.empty() && g_reserved.empty(), "memory left after the trim");
+}
+
+}  // namespace
+
+int main(int argc, char** argv) {
+  const char* name = argc > 1 ? argv[1] : "";
+  if (!strcmp(name, "release_beside_grow")) release_beside_grow();
+  else if (!strcmp(name, "many_threads")) many_threads();
+  else fail("no such scenario");
+  printf("ok\n");
+  return 0;
+}

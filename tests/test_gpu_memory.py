@@ -36,3 +36,26 @@ def test_threads_share_released_buffers(variant):
         assert len(out[k]) == 6
         for got in out[k]:
             assert all(np.array_equal(a, b) for a, b in zip(got, alone[k]))
+
+
+def test_threads_release_large_buffers():
+    """Value buffers of several mapped chunks of 256 MB (343 atoms in three
+    directions), released by one thread while another one grows its own."""
+    systems = [W.config_system("cube20", L=7, seed=3 + k) for k in range(2)]
+    opts = dict(skip="bound")
+    alone = [matrices(T.solve(s, **opts)[0]) for s in systems]
+    # stored blocks (16 x 16 FP64 values of four matrices) of the iterate
+    assert all(m[1].size * 4 * 2048 > 256 << 20 for m in alone)
+    same = [[] for _ in systems]
+
+    def work(k):
+        for _ in range(3):
+            got = matrices(T.solve(systems[k], **opts)[0])
+            same[k].append(all(np.array_equal(a, b) for a, b in zip(got, alone[k])))
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(len(systems))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert same == [[True] * 3] * 2
