@@ -28,6 +28,7 @@ constexpr size_t VM_MIN = (size_t)64 << 20;
 hipError_t vm_grow(DBuf& b, size_t n);     // map up to >= n bytes, contents kept
 void vm_release(DBuf& b);                  // chunks back to the pool, range freed
 void pool_trim();                          // pooled chunks of the device to the GPU driver
+bool device_wait();                        // for all work of the device; captures go on
 
 struct DBuf {
   void* p = nullptr;
@@ -322,6 +323,7 @@ struct tc2_ctx {
   // graph-captured updates (tiled kernel): one executable graph per iterate
   // buffer, valid while the key (buffers, sizes, kind, shape) is unchanged
   int graph = 0;                  // option: capture updates in hipGraphs
+  hipStream_t cap = nullptr;      // captures update graphs (launched on the run's stream)
   bool graph_ok = true;           // false after a capture the runtime refused
   hipGraphExec_t gexec[2] = {nullptr, nullptr};
   hipGraphExec_t gexec_post[2] = {nullptr, nullptr};  // profiling: the part after the products

@@ -368,7 +368,7 @@ tc2_status export_rows_impl(tc2_ctx* ctx, int32_t system, const int32_t* rows, i
   HIPCHK(hipStreamSynchronize(ctx->run.st ? ctx->run.st : st));
   const int c = ctx->cur, D = ctx->D, b = ctx->b, nb = ctx->nb;
   std::vector<int> rp(nb + 1);
-  HIPCHK(hipMemcpy(rp.data(), ctx->rp[c].p, (size_t)(nb + 1) * 4, hipMemcpyDeviceToHost));
+  HIPCHK(hipMemcpyWithStream(rp.data(), ctx->rp[c].p, (size_t)(nb + 1) * 4, hipMemcpyDeviceToHost, st));
   std::vector<char> want(si.nb, 0);
   for (int i = 0; i < n_rows; ++i) want[rows[i]] = 1;
   // entries of the wanted rows, in row order
@@ -380,7 +380,9 @@ tc2_status export_rows_impl(tc2_ctx* ctx, int32_t system, const int32_t* rows, i
     if (!want[i]) continue;
     const int I = si.row0 + i, n = rp[I + 1] - rp[I];
     std::vector<int> cs(n);
-    if (n) HIPCHK(hipMemcpy(cs.data(), ctx->ci[c].as<int>() + rp[I], (size_t)n * 4, hipMemcpyDeviceToHost));
+    if (n)
+      HIPCHK(hipMemcpyWithStream(cs.data(), ctx->ci[c].as<int>() + rp[I], (size_t)n * 4,
+                                 hipMemcpyDeviceToHost, st));
     for (int k = 0; k < n; ++k) {
       ent.push_back((long long)rp[I] + k);
       col.push_back(cs[k] - si.row0);
@@ -394,7 +396,7 @@ tc2_status export_rows_impl(tc2_ctx* ctx, int32_t system, const int32_t* rows, i
     Tmp dent, dout;
     HIPCHK(dent.alloc((size_t)ne * 8));
     HIPCHK(dout.alloc(vals.size() * 8));
-    HIPCHK(hipMemcpy(dent.p, ent.data(), (size_t)ne * 8, hipMemcpyHostToDevice));
+    HIPCHK(hipMemcpyWithStream(dent.p, ent.data(), (size_t)ne * 8, hipMemcpyHostToDevice, st));
     const long long total = (long long)vals.size();
     const unsigned g = (unsigned)std::min<long long>((total + 255) / 256, 1 << 20);
     if (ctx->cur_prec == P_FP64)
@@ -443,9 +445,10 @@ tc2_status export_entries_impl(tc2_ctx* ctx, int32_t matrix, int64_t first, int6
   HIPCHK(hipStreamSynchronize(ctx->run.st ? ctx->run.st : st));
   if (rows || cols) {
     std::vector<int> rp(nb + 1);
-    HIPCHK(hipMemcpy(rp.data(), ctx->rp[c].p, (size_t)(nb + 1) * 4, hipMemcpyDeviceToHost));
+    HIPCHK(hipMemcpyWithStream(rp.data(), ctx->rp[c].p, (size_t)(nb + 1) * 4, hipMemcpyDeviceToHost, st));
     if (cols)
-      HIPCHK(hipMemcpy(cols, ctx->ci[c].as<int>() + first, (size_t)count * 4, hipMemcpyDeviceToHost));
+      HIPCHK(hipMemcpyWithStream(cols, ctx->ci[c].as<int>() + first, (size_t)count * 4,
+                                 hipMemcpyDeviceToHost, st));
     if (rows) {
       int I = (int)(std::upper_bound(rp.begin(), rp.end(), (int)first) - rp.begin()) - 1;
       for (int64_t k = 0; k < count; ++k) {

@@ -141,6 +141,23 @@ void give(Small& S, void* p, size_t n) {
 
 }  // namespace
 
+// Wait for all work of the current device, by the wait that hipFree does.
+// hipDeviceSynchronize fails while another thread captures a graph, without
+// having waited, and ends that capture; a copy by hipMemcpy does the same (copies
+// go through hipMemcpyWithStream therefore).
+bool device_wait() {
+  void* p = nullptr;
+  hipError_t e = hipMalloc(&p, 256);
+  if (e == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
+    pool_trim();
+    e = hipMalloc(&p, 256);
+  }
+  if (e == hipSuccess) e = hipFree(p);
+  if (e != hipSuccess) (void)hipGetLastError();
+  return e == hipSuccess;
+}
+
 // Return every pooled chunk and free buffer of the current device to the GPU driver.
 void pool_trim() {
   int dev = 0;
@@ -221,13 +238,12 @@ void dev_free(void* p) {
         if (t_scope->idle || put(t_scope->free, p, n)) return;
       }
       if (dev != cur) (void)hipSetDevice(dev);
-      const bool done = hipDeviceSynchronize() == hipSuccess;
+      const bool done = device_wait();
       if (dev != cur) (void)hipSetDevice(cur);
       if (done) {
         give(S, p, n);
         return;
       }
-      (void)hipGetLastError();
       std::lock_guard<std::mutex> g(S.m);
       S.used.erase(p);
       break;
@@ -244,10 +260,7 @@ void MemScope::open(hipStream_t s) {
 }
 
 void MemScope::open_idle() {
-  if (hipDeviceSynchronize() != hipSuccess) {
-    (void)hipGetLastError();
-    return;
-  }
+  if (!device_wait()) return;
   idle = true;
   open(nullptr);
 }
@@ -341,7 +354,7 @@ void vm_release(DBuf& b) {
   int cur = 0;
   (void)hipGetDevice(&cur);
   if (cur != b.dev) (void)hipSetDevice(b.dev);
-  (void)hipDeviceSynchronize();
+  (void)device_wait();
   Pool& P = g_pool[b.dev];
   for (size_t k = 1; k < b.chunks.size(); ++k) (void)hipMemUnmap((char*)b.p + k * P.chunk, P.chunk);
   bool kept = false;

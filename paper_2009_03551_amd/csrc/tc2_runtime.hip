@@ -82,7 +82,8 @@ void pack_blocks(const tc2_bsr& m, int b, std::vector<double>& out) {
 template <typename T>
 tc2_status upload(tc2_ctx* ctx, DBuf& d, const std::vector<T>& h) {
   HIPCHK(d.reserve(h.size() * sizeof(T)));
-  if (!h.empty()) HIPCHK(hipMemcpy(d.p, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice));
+  if (!h.empty())
+    HIPCHK(hipMemcpyWithStream(d.p, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice, ctx->own));
   return TC2_OK;
 }
 
@@ -176,6 +177,7 @@ void tc2_free(tc2_ctx* ctx) {
   if (!ctx) return;
   (void)hipSetDevice(ctx->device);
   if (ctx->own) (void)hipStreamDestroy(ctx->own);
+  if (ctx->cap) (void)hipStreamDestroy(ctx->cap);
   for (hipEvent_t& e : ctx->pev)
     if (e) (void)hipEventDestroy(e);
   for (hipGraphExec_t& g : ctx->gexec)
@@ -560,7 +562,7 @@ static tc2_status setup_impl(const tc2_problem* probs, int32_t np, const tc2_opt
   }
   if (ctx->rowlo.reserve((size_t)ctx->nb * b * 8) || ctx->rowhi.reserve((size_t)ctx->nb * b * 8))
     return fail(TC2_ENOMEM);
-  if (hipDeviceSynchronize() != hipSuccess) return fail(TC2_EDEVICE);
+  if (hipStreamSynchronize(ctx->own) != hipSuccess) return fail(TC2_EDEVICE);
   *out = ctx;
   return TC2_OK;
 }
@@ -1248,7 +1250,8 @@ int step_graph(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
         (uintptr_t)ctx->tile_cnt.p, (uintptr_t)ctx->tile_rp.p, (uintptr_t)ctx->tile_pairs.p,
         (uintptr_t)ctx->tile_bits.p, (uintptr_t)ctx->nominal.p, (uintptr_t)ctx->mask[c].p,
         (uintptr_t)ctx->mask[n].p, (uintptr_t)ctx->sum_rows.p, (uintptr_t)ctx->pin_graph.p};
-    // the three parts of the update, as stream work (captured or not)
+    // the three parts of the update, as work of stream rs (captured or not)
+    hipStream_t rs = st;
     auto rec_pre = [&]() {
       PanelArgs pa{};
       pa.nc = nc;
@@ -1276,14 +1279,14 @@ int step_graph(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
       pa.tile_bits = ctx->tile_bits.as<unsigned>();
       pa.tile_words = tile_words;
       pa.nominal = ctx->nominal.as<unsigned long long>();
-      launch_panels(st, pa,
+      launch_panels(rs, pa,
                     ClearArgs{{cnt, ctx->exec_pairs.as<int>(), ctx->rowcnt.as<int>(),
                                ctx->cursor.as<int>(), ctx->nominal.as<int>(),
                                screen ? ctx->screened.as<int>() : nullptr},
                               {8, 2, nb, nb, 2LL * ctx->nsys, screen ? 4 : 0}});
-      launch_tiles(st, pa, mult, ctx->sys_lo.as<int>(), ctx->sys_hi.as<int>());
+      launch_tiles(rs, pa, mult, ctx->sys_lo.as<int>(), ctx->sys_hi.as<int>());
       if (screen && !norms_ready)
-        launch_block_norms(st, ctx->cur_prec, cap_c, D, ctx->xv[c].p, ctx->bn.as<float>(),
+        launch_block_norms(rs, ctx->cur_prec, cap_c, D, ctx->xv[c].p, ctx->bn.as<float>(),
                            ctx->rp[c].as<int>() + nb);
     };
     auto rec_num = [&]() -> bool {
@@ -1335,7 +1338,7 @@ int step_graph(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
       ta.screened = screen ? ctx->screened.as<unsigned long long>() : nullptr;
       ta.mlp_skipped = screen ? ctx->screened.as<unsigned long long>() + 1 : nullptr;
       ta.kl_chunk = ctx->test_kl_chunk;
-      return launch_tile_numeric(st, ctx->cur_prec, ta);
+      return launch_tile_numeric(rs, ctx->cur_prec, ta);
     };
     auto rec_post = [&]() {
       if (any_stopped) {
@@ -1353,7 +1356,7 @@ int step_graph(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
         ca.stage_cap = cap;
         ca.overflow = cnt + 2;
         ca.rowcnt = ctx->rowcnt.as<int>();
-        launch_copy_through(st, ctx->cur_prec, ca, (int)cap_c);
+        launch_copy_through(rs, ctx->cur_prec, ca, (int)cap_c);
       }
       CompactArgs cm{};
       cm.nb = nb;
@@ -1370,17 +1373,17 @@ int step_graph(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
       cm.tmp_src = ctx->tmp_src.as<int>();
       cm.new_ci = ctx->ci[n].as<int>();
       cm.new_src = ctx->new_src.as<int>();
-      launch_scan(st, nb, ctx->rowcnt.as<int>(), ctx->rp[n].as<int>(), cnt);
-      launch_compact_scatter(st, cm, cap);
-      launch_row_sort(st, cm);
+      launch_scan(rs, nb, ctx->rowcnt.as<int>(), ctx->rp[n].as<int>(), cnt);
+      launch_compact_scatter(rs, cm, cap);
+      launch_row_sort(rs, cm);
       // the gather (with the masks of the new values) writes over the current
       // values: skipped when the stage overflowed (the update is then run
       // again from those values)
-      launch_gather_masks(st, ctx->cur_prec, (long long)cap2, D, ctx->new_src.as<int>(),
+      launch_gather_masks(rs, ctx->cur_prec, (long long)cap2, D, ctx->new_src.as<int>(),
                           ctx->stage.p, ctx->xv[c].p, ctx->mask[n].as<unsigned char>(),
                           screen ? ctx->bn.as<float>() : nullptr, ctx->rp[n].as<int>() + nb,
                           cnt + 2);
-      launch_reduce(st, ctx->nsys, ctx->sys_lo.as<int>(), ctx->sys_hi.as<int>(),
+      launch_reduce(rs, ctx->nsys, ctx->sys_lo.as<int>(), ctx->sys_hi.as<int>(),
                     ctx->partial.as<double>(), ctx->scal.as<double>());
       if (dl) {
         // branch and stopping decisions for the next update, on the device
@@ -1399,27 +1402,37 @@ int step_graph(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
         da.active = ctx->active.as<int>();
         da.branch = ctx->branch.as<int>();
         da.word = ctx->dl_word.as<DecideWord>();
-        launch_decide(st, da);
+        launch_decide(rs, da);
       } else {
-        hipLaunchKernelGGL(k_report, dim3(1), dim3(256), 0, st, cnt,
+        hipLaunchKernelGGL(k_report, dim3(1), dim3(256), 0, rs, cnt,
                            ctx->exec_pairs.as<unsigned long long>(), ctx->rp[n].as<int>() + nb,
                            screen ? ctx->screened.as<unsigned long long>() : nullptr, ctx->nsys * NQ,
                            ctx->scal.as<double>(), (char*)ctx->pin_graph.p);
       }
     };
-    // capture of a part sequence into an executable graph; false if refused
-    auto capture = [&](hipGraphExec_t* out, bool with_pre, bool with_num, bool with_post) {
-      if (hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal) != hipSuccess) {
+    // Capture of a part sequence into an executable graph; false if refused.  On
+    // a stream of its own: a device-wide wait by another thread ends the capture,
+    // and its stream then takes no more work (so the capture is tried again on a
+    // new one), while the caller's stream goes on.
+    auto capture_once = [&](hipGraphExec_t* out, bool with_pre, bool with_num, bool with_post) {
+      if (!ctx->cap && hipStreamCreateWithFlags(&ctx->cap, hipStreamNonBlocking) != hipSuccess) {
+        (void)hipGetLastError();
+        ctx->cap = nullptr;
+        return false;
+      }
+      if (hipStreamBeginCapture(ctx->cap, hipStreamCaptureModeThreadLocal) != hipSuccess) {
         (void)hipGetLastError();
         return false;
       }
       bool ok = true;
+      rs = ctx->cap;
       if (with_pre) rec_pre();
       if (with_num) ok = rec_num();
       if (with_post) rec_post();
+      rs = st;
       if (hipGetLastError() != hipSuccess) ok = false;
       hipGraph_t graph = nullptr;
-      const hipError_t ee = hipStreamEndCapture(st, &graph);
+      const hipError_t ee = hipStreamEndCapture(ctx->cap, &graph);
       if (ee != hipSuccess || !ok || !graph) {
         if (graph) (void)hipGraphDestroy(graph);
         (void)hipGetLastError();
@@ -1433,6 +1446,15 @@ int step_graph(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
         return false;
       }
       return true;
+    };
+    auto capture = [&](hipGraphExec_t* out, bool with_pre, bool with_num, bool with_post) {
+      for (int k = 0; k < 3; ++k) {
+        if (capture_once(out, with_pre, with_num, with_post)) return true;
+        if (ctx->cap) (void)hipStreamDestroy(ctx->cap);
+        ctx->cap = nullptr;
+        (void)hipGetLastError();
+      }
+      return false;
     };
     // one graph for the whole update; when profiling, the products run as a
     // direct launch between a graph before and a graph after them, so that
@@ -2263,9 +2285,10 @@ extern "C" int64_t tc2_log_copy(tc2_ctx* ctx, float* x, float* y, float* z, int6
   if (hipSetDevice(ctx->device) != hipSuccess) return TC2_EDEVICE;
   const long long n = std::min<long long>(ctx->log_n, cap);
   if (n == 0) return 0;
-  if (hipMemcpy(x, ctx->log_x.p, (size_t)n * MLP_NF * 4, hipMemcpyDeviceToHost) != hipSuccess ||
-      hipMemcpy(y, ctx->log_y.p, (size_t)n * 4, hipMemcpyDeviceToHost) != hipSuccess ||
-      (z && hipMemcpy(z, ctx->log_z.p, (size_t)n * 4, hipMemcpyDeviceToHost) != hipSuccess))
+  auto take = [&](float* to, const tc2::DBuf& from, long long count) {
+    return hipMemcpyWithStream(to, from.p, (size_t)count * 4, hipMemcpyDeviceToHost, ctx->own) == hipSuccess;
+  };
+  if (!take(x, ctx->log_x, n * MLP_NF) || !take(y, ctx->log_y, n) || (z && !take(z, ctx->log_z, n)))
     return TC2_EDEVICE;
   return n;
 }

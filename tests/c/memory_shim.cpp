@@ -37,6 +37,8 @@ std::map<uint64_t, size_t> g_chunk;          // chunk -> bytes
 uint64_t g_next_chunk = 1;
 std::atomic<int> g_stream_waits{0}, g_device_waits{0};
 std::function<void(void*)> g_on_unmap;       // before a mapping is taken away
+std::atomic<bool> g_busy{false};             // work in flight: no buffer may be handed on
+std::atomic<bool> g_capture{false};          // another thread captures a graph
 
 // calls of every kind that the pool makes, in the model
 bool chunk_mapped(uint64_t h) {
@@ -52,7 +54,11 @@ extern "C" {
 hipError_t hipGetDevice(int* d) { return *d = 0, hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
-hipError_t hipDeviceSynchronize() { return ++g_device_waits, hipSuccess; }
+hipError_t hipDeviceSynchronize() {
+  check(!g_capture, "a capture of another thread ended by a device-wide wait");
+  g_busy = false;
+  return ++g_device_waits, hipSuccess;
+}
 hipError_t hipStreamSynchronize(hipStream_t) { return ++g_stream_waits, hipSuccess; }
 hipError_t hipDeviceTotalMem(size_t* n, hipDevice_t) { return *n = g_capacity, hipSuccess; }
 
@@ -71,6 +77,7 @@ hipError_t hipFree(void* p) {
   check(it != g_alloc.end(), "hipFree of an address that is not allocated");
   g_in_use -= it->second;
   g_alloc.erase(it);
+  g_busy = false;  // hipFree waits for the device
   return hipSuccess;
 }
 hipError_t hipMemGetAllocationGranularity(size_t* g, const hipMemAllocationProp*,
@@ -119,6 +126,7 @@ hipError_t hipMemMap(void* p, size_t, size_t, hipMemGenericAllocationHandle_t h,
   return hipSuccess;
 }
 hipError_t hipMemUnmap(void* p, size_t) {
+  check(!g_busy, "a chunk unmapped with work in flight");
   if (g_on_unmap) g_on_unmap(p);
   std::lock_guard<std::mutex> g(g_m);
   check(g_mapped.erase((uintptr_t)p) == 1, "unmapped where nothing is mapped");
@@ -195,12 +203,40 @@ void many_threads() {
   check(g_in_use == 0 && g_mapped.empty() && g_reserved.empty(), "memory left after the trim");
 }
 
+// Buffers of every size released while work is in flight and another thread
+// captures a graph: none is handed on before the work has ended.
+void release_beside_capture() {
+  for (size_t n : {4096 * (size_t)1, 3 * MB, 60 * MB, 300 * MB, 900 * MB}) {
+    DBuf b;
+    check(b.reserve(n) == hipSuccess, "reserve");
+    g_busy = g_capture = true;
+    b.release();
+    check(!g_busy, "a buffer handed on with work in flight");
+    g_capture = false;
+  }
+  g_busy = g_capture = true;
+  {
+    MemScope scope;
+    scope.open_idle();
+    check(!g_busy && scope.is_open, "a context released with work in flight");
+  }
+  // the same with no memory left for the wait
+  DBuf keep, b;
+  check(keep.reserve(4096) == hipSuccess && b.reserve(700 * MB) == hipSuccess, "reserve");
+  keep.release();
+  g_capacity = g_in_use;
+  g_busy = true;
+  b.release();
+  check(!g_busy, "a buffer handed on with work in flight, memory full");
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const char* name = argc > 1 ? argv[1] : "";
   if (!strcmp(name, "release_beside_grow")) release_beside_grow();
   else if (!strcmp(name, "many_threads")) many_threads();
+  else if (!strcmp(name, "release_beside_capture")) release_beside_capture();
   else fail("no such scenario");
   printf("ok\n");
   return 0;

@@ -31,3 +31,7 @@ def test_a_range_is_handed_on_only_when_its_chunks_are_unmapped(shim):
 
 def test_threads_grow_and_release(shim):
     shim("many_threads")
+
+
+def test_releases_wait_and_leave_captures_of_other_threads_alone(shim):
+    shim("release_beside_capture")
