@@ -343,7 +343,8 @@ TC2_API void tc2_free(tc2_ctx *ctx);
    chunks a buffer or a freed context gives back stay in a per-device pool of
    the process and are mapped again by later buffers and contexts, so that
    the GPU driver does not clear reclaimed memory before each reuse.  Small
-   buffers are kept likewise, at most 256 MB per device.  The pool
+   buffers are kept likewise, at most 256 MB per device, and as much by each
+   orthogonalisation or congruence while it runs.  The pool
    is returned to the GPU driver when an allocation of the library fails for lack
    of memory (then retried), and by this call: device = HIP ordinal.  Returns
    TC2_EINVAL for an ordinal without a device.  Call it when other code of the

@@ -259,11 +259,13 @@ void dev_free(void* p);  // as hipFree: waits for the device (see MemScope)
 
 // Buffers of this thread that dev_free releases while a scope is open are not
 // waited for one by one.  open: they serve this thread's later dev_mallocs,
-// whose uses follow on the same stream, and the wait is at the scope's end.
+// whose uses follow on the same stream, and the wait is at the scope's end
+// (earlier when they are many, or memory is short: drain).
 // open_idle: the device is idle, and nothing is launched in the scope.
 typedef std::map<size_t, std::vector<void*>> SizeLists;
 struct MemScope {
   SizeLists free;
+  size_t held = 0;  // bytes in free
   hipStream_t st = nullptr;
   int dev = 0;
   bool is_open = false, idle = false;
@@ -274,6 +276,7 @@ struct MemScope {
   ~MemScope();
   void open(hipStream_t s);
   void open_idle();
+  bool drain();
 };
 
 // kernels (launch wrappers), all asynchronous on `st`

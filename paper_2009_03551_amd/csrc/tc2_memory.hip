@@ -23,7 +23,8 @@
 // As with hipFree, the device is idle before a released buffer can be another's
 // (dev_free waits for it), except where one wait serves many: within a MemScope
 // of a stream, buffers pass from one use to the next in the order of that
-// stream, and leave the scope once the stream has ended.
+// stream, and leave the scope once the stream has ended: at its end, when they
+// are more than SMALL_HELD, and when an allocation fails for lack of memory.
 #include "tc2_context.h"
 
 #include <map>
@@ -158,9 +159,13 @@ bool device_wait() {
   return e == hipSuccess;
 }
 
-// Return every pooled chunk and free buffer of the current device to the GPU driver.
+// Return every pooled chunk and free buffer of the current device to the GPU
+// driver, those of this thread's open scopes included.
 void pool_trim() {
   int dev = 0;
+  if (hipGetDevice(&dev) == hipSuccess)
+    for (MemScope* s = t_scope; s; s = s->outer)
+      if (s->dev == dev) (void)s->drain();
   Pool* P = pool_of(&dev);
   if (P) {
     std::lock_guard<std::mutex> g(P->m);
@@ -191,7 +196,10 @@ hipError_t dev_malloc(void** p, size_t n) {
   size_t want = n;
   if (small) {
     want = small_size(n);
-    if (t_scope && t_scope->dev == dev && (*p = take(t_scope->free, want))) return hipSuccess;
+    if (t_scope && t_scope->dev == dev && (*p = take(t_scope->free, want))) {
+      t_scope->held -= want;
+      return hipSuccess;
+    }
     Small& S = g_small[dev];
     std::lock_guard<std::mutex> g(S.m);
     if ((*p = take(S.free, want))) {
@@ -234,8 +242,14 @@ void dev_free(void* p) {
         n = it->second;
       }
       if (t_scope && t_scope->dev == dev) {
-        if (t_scope->idle) give(S, p, n);
-        if (t_scope->idle || put(t_scope->free, p, n)) return;
+        if (t_scope->idle) {
+          give(S, p, n);
+          return;
+        }
+        if (put(t_scope->free, p, n)) {
+          if ((t_scope->held += n) > SMALL_HELD) (void)t_scope->drain();
+          return;
+        }
       }
       if (dev != cur) (void)hipSetDevice(dev);
       const bool done = device_wait();
@@ -265,17 +279,26 @@ void MemScope::open_idle() {
   open(nullptr);
 }
 
+// The free buffers to the pool, once the stream has ended; false when it failed.
+bool MemScope::drain() {
+  if (held == 0) return true;
+  if (hipStreamSynchronize(st) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  for (auto& l : free)
+    for (void* p : l.second) give(g_small[dev], p, l.first);
+  free.clear();
+  held = 0;
+  return true;
+}
+
 MemScope::~MemScope() {
   if (!is_open) return;
   t_scope = outer;
-  const bool any = !free.empty();
-  const bool done = !any || hipStreamSynchronize(st) == hipSuccess;
-  if (!done) (void)hipGetLastError();
+  if (drain()) return;
   for (auto& l : free)
-    for (void* p : l.second) {
-      if (done) give(g_small[dev], p, l.first);
-      else dev_free(p);
-    }
+    for (void* p : l.second) dev_free(p);
 }
 
 // Grow the virtual range of b to at least n bytes, keeping what is mapped.

@@ -203,6 +203,53 @@ void many_threads() {
   check(g_in_use == 0 && g_mapped.empty() && g_reserved.empty(), "memory left after the trim");
 }
 
+// Buffers released within a scope: given back when an allocation fails for lack
+// of memory, once the scope's stream has ended, and at most 256 MB of them held.
+void scope_under_pressure() {
+  g_capacity = 2 * GB;
+  {
+    MemScope scope;
+    scope.open((hipStream_t)0x1);
+    // released buffers of one size class serve later ones of that class only
+    for (size_t n : {40 * MB, 48 * MB, 56 * MB, 63 * MB}) {
+      void* p[4];
+      for (void*& q : p) check(dev_malloc(&q, n) == hipSuccess, "small buffer");
+      for (void* q : p) dev_free(q);
+      size_t held = 0;
+      for (auto& a : g_alloc) held += a.second;
+      check(held <= 2 * 256 * MB, "released buffers held without bound");
+    }
+    void* p = nullptr;
+    const int waits = g_stream_waits;
+    check(dev_malloc(&p, 2 * GB) == hipSuccess, "memory that the scope holds was not given back");
+    check(g_stream_waits > waits, "buffers given back before the stream had ended");
+    dev_free(p);
+    // the same for a buffer of mapped chunks
+    void* q[4];
+    for (void*& v : q) check(dev_malloc(&v, 60 * MB) == hipSuccess, "small buffer");
+    for (void* v : q) dev_free(v);
+    DBuf b;
+    check(b.reserve(2 * GB) == hipSuccess, "memory that the scope holds was not given back");
+    b.release();
+    // an inner scope's failure reaches the outer one
+    for (void*& v : q) check(dev_malloc(&v, 60 * MB) == hipSuccess, "small buffer");
+    for (void* v : q) dev_free(v);
+    {
+      MemScope inner;
+      inner.open((hipStream_t)0x2);
+      check(dev_malloc(&p, 2 * GB) == hipSuccess, "memory of the outer scope was not given back");
+      dev_free(p);
+    }
+    // and buffers still pass from one use to the next
+    check(dev_malloc(&p, 8 * MB) == hipSuccess, "small buffer");
+    dev_free(p);
+    check(dev_malloc(&q[0], 8 * MB) == hipSuccess && q[0] == p, "a released buffer was not reused");
+    dev_free(q[0]);
+  }
+  pool_trim();
+  check(g_in_use == 0, "memory left after the trim");
+}
+
 // Buffers of every size released while work is in flight and another thread
 // captures a graph: none is handed on before the work has ended.
 void release_beside_capture() {
@@ -236,6 +283,7 @@ int main(int argc, char** argv) {
   const char* name = argc > 1 ? argv[1] : "";
   if (!strcmp(name, "release_beside_grow")) release_beside_grow();
   else if (!strcmp(name, "many_threads")) many_threads();
+  else if (!strcmp(name, "scope_under_pressure")) scope_under_pressure();
   else if (!strcmp(name, "release_beside_capture")) release_beside_capture();
   else fail("no such scenario");
   printf("ok\n");

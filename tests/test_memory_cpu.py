@@ -35,3 +35,7 @@ def test_threads_grow_and_release(shim):
 
 def test_releases_wait_and_leave_captures_of_other_threads_alone(shim):
     shim("release_beside_capture")
+
+
+def test_released_buffers_of_a_scope_are_bounded_and_given_back(shim):
+    shim("scope_under_pressure")
