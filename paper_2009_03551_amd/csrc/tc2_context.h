@@ -312,6 +312,7 @@ struct tc2_ctx {
   // tiled kernel, and a tiny stage that overflows every update
   int test_kl_chunk = 0;
   int test_fine_subs = tc2::FINE_SUBS;  // fewer: sub-tiles not split into parts
+  size_t panel_bound = tc2::VM_MIN;  // panel buffers counted, not bounded, from this size on
   long long test_stage_cap = 0;
   int test_no_zero_skip = 0;      // issue every product (masks not passed to the kernel)
   int test_waves_per_column = 0;  // 1: trace sums grouped by sub-tile column in every numeric kernel

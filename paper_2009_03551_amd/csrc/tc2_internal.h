@@ -295,8 +295,10 @@ void launch_items(hipStream_t st, int nb, const int* cand_rp, const int* item_rp
 void launch_items_count(hipStream_t st, int nb, const int* cand_rp, int* item_cnt);
 void launch_numeric(hipStream_t st, int prec, const NumArgs& a);
 void launch_measure(hipStream_t st, int prec, const MeasArgs& a);
-// clears, then panels and tile counts; tiles (and, for mult > 0, the systems' items)
-void launch_panels(hipStream_t st, const PanelArgs& a, const ClearArgs& clear);
+// clears and panel counts; panels and tile counts; tiles (and, for mult > 0, the
+// systems' items)
+void launch_panel_count(hipStream_t st, const PanelArgs& a, const ClearArgs& clear);
+void launch_panels(hipStream_t st, const PanelArgs& a);
 void launch_tiles(hipStream_t st, const PanelArgs& a, int mult, int* sys_lo, int* sys_hi);
 void launch_clear(hipStream_t st, const ClearArgs& a);
 bool launch_tile_numeric(hipStream_t st, int prec, const TileArgs& a);  // false: no such shape

@@ -359,6 +359,7 @@ static tc2_status setup_impl(const tc2_problem* probs, int32_t np, const tc2_opt
   if (const char* v = getenv("TC2_TEST_KL_CHUNK")) ctx->test_kl_chunk = std::max(0, atoi(v));
   if (const char* v = getenv("TC2_TEST_FINE_SUBS"))
     ctx->test_fine_subs = std::min(std::max(0, atoi(v)), FINE_SUBS);
+  if (const char* v = getenv("TC2_TEST_PANEL_BOUND")) ctx->panel_bound = (size_t)std::max(0LL, atoll(v));
   if (const char* v = getenv("TC2_TEST_STAGE_CAP")) ctx->test_stage_cap = std::max(0LL, atoll(v));
   if (const char* v = getenv("TC2_TEST_NO_ZERO_SKIP")) ctx->test_no_zero_skip = atoi(v) != 0;
   if (const char* v = getenv("TC2_TEST_WAVES_PER_COLUMN")) ctx->test_waves_per_column = atoi(v);
@@ -743,14 +744,28 @@ tc2_status step(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
     pa.tile_words = (ctx->max_sys_clusters + 31) / 32;
     HIPCHK(ctx->tile_bits.reserve((size_t)std::max(nc, 1) * pa.tile_words * 4));
     pa.tile_bits = ctx->tile_bits.as<unsigned>();
-    // a panel column is that of at least one entry
-    const size_t ent = (size_t)std::max(ctx->nnz[c], 1);
-    HIPCHK(ctx->panel_k.reserve_grow(ent * 4));
-    HIPCHK(ctx->panel_e.reserve_grow(ent * CS * 4));
+    pa.nominal = ctx->nominal.as<unsigned long long>();
+    launch_panel_count(st, pa, ClearArgs{{ctx->nominal.as<int>()}, {2LL * ctx->nsys}});
+    // a panel column is that of at least one entry; where that bound takes more
+    // than panel_bound bytes (values of 2 KB or more per entry then fill
+    // gigabytes), the columns are counted, for one more read-back
+    size_t cols = (size_t)std::max(ctx->nnz[c], 1);
+    if (cols * CS * 4 >= ctx->panel_bound) {
+      std::vector<int> pc(nc);
+      HIPCHK(hipMemcpyAsync(pc.data(), ctx->panel_cnt.p, (size_t)nc * 4, hipMemcpyDeviceToHost, st));
+      HIPCHK(hipStreamSynchronize(st));
+      cols = 0;
+      for (int v : pc) cols += (size_t)v;
+      cols = std::max<size_t>(cols, 1);
+      HIPCHK(ctx->panel_k.reserve(cols * 4));
+      HIPCHK(ctx->panel_e.reserve(cols * CS * 4));
+    } else {
+      HIPCHK(ctx->panel_k.reserve_grow(cols * 4));
+      HIPCHK(ctx->panel_e.reserve_grow(cols * CS * 4));
+    }
     pa.panel_k = ctx->panel_k.as<int>();
     pa.panel_e = ctx->panel_e.as<int>();
-    pa.nominal = ctx->nominal.as<unsigned long long>();
-    launch_panels(st, pa, ClearArgs{{ctx->nominal.as<int>()}, {2LL * ctx->nsys}});
+    launch_panels(st, pa);
     std::vector<long long> pairs(nc);
     std::vector<int> tiles(nc);
     HIPCHK(hipMemcpyAsync(tiles.data(), ctx->tile_cnt.p, (size_t)nc * 4, hipMemcpyDeviceToHost, st));
@@ -1279,11 +1294,12 @@ int step_graph(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
       pa.tile_bits = ctx->tile_bits.as<unsigned>();
       pa.tile_words = tile_words;
       pa.nominal = ctx->nominal.as<unsigned long long>();
-      launch_panels(rs, pa,
-                    ClearArgs{{cnt, ctx->exec_pairs.as<int>(), ctx->rowcnt.as<int>(),
-                               ctx->cursor.as<int>(), ctx->nominal.as<int>(),
-                               screen ? ctx->screened.as<int>() : nullptr},
-                              {8, 2, nb, nb, 2LL * ctx->nsys, screen ? 4 : 0}});
+      launch_panel_count(rs, pa,
+                         ClearArgs{{cnt, ctx->exec_pairs.as<int>(), ctx->rowcnt.as<int>(),
+                                    ctx->cursor.as<int>(), ctx->nominal.as<int>(),
+                                    screen ? ctx->screened.as<int>() : nullptr},
+                                   {8, 2, nb, nb, 2LL * ctx->nsys, screen ? 4 : 0}});
+      launch_panels(rs, pa);
       launch_tiles(rs, pa, mult, ctx->sys_lo.as<int>(), ctx->sys_hi.as<int>());
       if (screen && !norms_ready)
         launch_block_norms(rs, ctx->cur_prec, cap_c, D, ctx->xv[c].p, ctx->bn.as<float>(),

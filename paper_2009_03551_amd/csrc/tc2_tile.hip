@@ -323,10 +323,15 @@ void launch_block_norms(hipStream_t st, int prec, long long nnz, int D, const vo
 }
 
 // ================================================================== launchers
-void launch_panels(hipStream_t st, const PanelArgs& a, const ClearArgs& clear) {
+void launch_panel_count(hipStream_t st, const PanelArgs& a, const ClearArgs& clear) {
   if (a.nc == 0) return;
   const size_t words = (size_t)((a.max_sys_atoms + 31) / 32);
   hipLaunchKernelGGL(k_panel_count, dim3(a.nc), dim3(PNT), words * 4, st, a, clear);
+}
+
+void launch_panels(hipStream_t st, const PanelArgs& a) {
+  if (a.nc == 0) return;
+  const size_t words = (size_t)((a.max_sys_atoms + 31) / 32);
   hipLaunchKernelGGL(k_panels, dim3(a.nc), dim3(PNT), std::max(2 * words, (size_t)a.tile_words) * 4, st,
                      a);
 }
