@@ -206,9 +206,17 @@ tc2_status tc2_trim_memory(int32_t device) {
 }
 
 // ---- tuned sub-tile shapes.  The cache file holds one JSON object per line,
-//   {"key": "<arch>/<kind>/D<d>/k<ksteps>/s<skip>", "shape": "<SPxTQ>", "ms": {...}}
+//   {"key": "<arch>/<kind>/D<d>/k<ksteps>/s<skip>", "shape": "<SPxTQ>", "kernel": n,
+//    "parts": p, "ms": {...}}
 // keyed by what changes the best shape: kernel kind, directions, K-steps per
-// block (block size) and screening.  Later lines win.
+// block (block size) and screening.  Later lines win.  A line with times is
+// taken only from the kernel that this one is (TUNE_KERNEL, raised when a change
+// of the numeric kernel may change the best shape); one without is a shape set
+// by hand.  parts is 1 when the update timed is so small that it runs in parts
+// of sub-tiles, where the shape decides next to nothing (and the best one for
+// few whole sub-tiles is another than for many): such a line serves contexts of
+// that size only.
+constexpr int TUNE_KERNEL = 2;
 static const char* kind_name(int k) {
   static const char* n[4] = {"fp64", "fp32", "bf16", "fp32w"};
   return n[k];
@@ -227,8 +235,11 @@ static void tune_load(tc2_ctx* ctx) {
   if (!f) return;
   std::string keys[4];
   for (int k = 0; k < 4; ++k) keys[k] = "\"key\": \"" + tune_key(ctx, k) + "\"";
+  const std::string made_by = "\"kernel\": " + std::to_string(TUNE_KERNEL) + ",";
   char line[1024];
   while (fgets(line, sizeof(line), f)) {
+    if (strstr(line, "\"ms\": {\"") && !strstr(line, made_by.c_str())) continue;
+    if (strstr(line, "\"parts\": 1,") && 2 * ctx->tile_bound > FINE_SUBS) continue;
     for (int k = 0; k < 4; ++k) {
       if (!strstr(line, keys[k].c_str())) continue;
       const char* p = strstr(line, "\"shape\": \"");
@@ -247,12 +258,12 @@ static void tune_load(tc2_ctx* ctx) {
   fclose(f);
 }
 
-static void tune_store(const tc2_ctx* ctx, int kind, const float* ms) {
+static void tune_store(const tc2_ctx* ctx, int kind, bool parts, const float* ms) {
   if (ctx->tune_cache.empty()) return;
   FILE* f = fopen(ctx->tune_cache.c_str(), "a");
   if (!f) return;
-  fprintf(f, "{\"key\": \"%s\", \"shape\": \"%s\", \"ms\": {", tune_key(ctx, kind).c_str(),
-          tile_shape_name(ctx->shape[kind]));
+  fprintf(f, "{\"key\": \"%s\", \"shape\": \"%s\", \"kernel\": %d, \"parts\": %d, \"ms\": {",
+          tune_key(ctx, kind).c_str(), tile_shape_name(ctx->shape[kind]), TUNE_KERNEL, parts ? 1 : 0);
   bool first = true;
   for (int sh = 0; sh < TS_N; ++sh) {
     if (ms[sh] < 0.f) continue;
@@ -355,7 +366,6 @@ static tc2_status setup_impl(const tc2_problem* probs, int32_t np, const tc2_opt
   if (o->metrics_log) ctx->metrics_log = o->metrics_log;
   ctx->arch = arch;
   for (int k = 0; k < 4; ++k) ctx->shape[k] = tile_shape_default(k, D);
-  if (ctx->tune) tune_load(ctx);
   if (const char* v = getenv("TC2_TEST_KL_CHUNK")) ctx->test_kl_chunk = std::max(0, atoi(v));
   if (const char* v = getenv("TC2_TEST_FINE_SUBS"))
     ctx->test_fine_subs = std::min(std::max(0, atoi(v)), FINE_SUBS);
@@ -519,6 +529,7 @@ static tc2_status setup_impl(const tc2_problem* probs, int32_t np, const tc2_opt
       const long long m = csys_end[s] - csys_start[s];
       ctx->tile_bound += m * (m + 1) / 2;
     }
+    if (ctx->tune) tune_load(ctx);
     // with fewer cluster pairs than compute units, one workgroup per pair
     // leaves most units idle and each runs the whole column loop of its
     // pair: the FP64 kind, 8x8 by default, then takes the 4x8 sub-tile (two
@@ -900,7 +911,8 @@ tc2_status step(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
     for (int sh = 0; sh < TS_N; ++sh) {
       ms_s[sh] = -1.f;
       if (!tile_shape_available(kind, D, sh)) continue;
-      const TileArgs ta = tile_args(cap, sh);
+      TileArgs ta = tile_args(cap, sh);
+      ta.fine_subs = 0;
       for (int rep = 0; rep < 2; ++rep) {
         launch_fill_int(st, cnt, 0, 8);
         launch_fill_int(st, ctx->exec_pairs.as<int>(), 0, 2);
@@ -927,8 +939,8 @@ tc2_status step(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
     (void)hipEventDestroy(t1);
     ctx->shape[kind] = best;
     ctx->tuned[kind] = true;
-    tune_store(ctx, kind, ms_s);
     mult = tile_subs(best);
+    tune_store(ctx, kind, (long long)n_work * mult <= FINE_SUBS, ms_s);
   }
   ctx->prev_out_bound = out_bound;
   if (tiled)

@@ -1,5 +1,7 @@
 """Routes that an update takes by the size of a problem, against each other on
 the same problem: the environment moves the limits between them."""
+import json
+
 import numpy as np
 import pytest
 
@@ -33,3 +35,41 @@ def test_panel_columns_counted_or_bounded(knob, sizes, bound):
     b = T.solve(s)
     for x, y in zip(a, b):
         same(x, y)
+
+
+def tuned(path, s, **kw):
+    r = T.solve(s, skip="bound", tune=True, tune_cache=str(path), **kw)[0]
+    return r, [json.loads(x) for x in path.read_text().splitlines()]
+
+
+def test_a_small_problem_is_tuned_by_whole_subtiles(tmp_path):
+    # 64 atoms run in parts of sub-tiles, the same for every shape; an 8 x 8
+    # sub-tile by one workgroup takes 1.8 times as long as its halves by two
+    # (0.20 ms against 0.11)
+    s = W.config_system("chain64")
+    ms = [tuned(tmp_path / f"t{k}", s)[1][0]["ms"] for k in range(3)]
+    assert min(m["8x8"] for m in ms) > 1.2 * max(m["8x4"] for m in ms), ms
+
+
+def test_a_shape_tuned_on_a_small_problem_stays_there(tmp_path):
+    small, large = W.config_system("cube10", L=4), W.config_system("cube10", L=8)
+    path = tmp_path / "tune"
+    a, lines = tuned(path, small)
+    assert len(lines) == 1 and lines[0]["parts"] == 1 and a.ms_tune > 0.0
+    b, lines = tuned(path, large, export=False)
+    assert len(lines) == 2 and lines[1]["parts"] == 0 and b.ms_tune > 0.0
+    c, lines = tuned(path, large, export=False)
+    assert len(lines) == 2 and c.ms_tune == 0.0 and c.tile_shape == b.tile_shape
+    d, lines = tuned(path, small)
+    assert len(lines) == 2 and d.ms_tune == 0.0
+
+
+def test_shapes_timed_with_another_kernel_are_timed_again(tmp_path):
+    s = W.config_system("cube10", L=4)
+    path = tmp_path / "tune"
+    path.write_text('{"key": "gfx950/fp64/D1/k4/s1", "shape": "8x4", '
+                    '"ms": {"8x8": 0.2, "4x8": 0.2, "8x4": 0.1}}\n')
+    a, lines = tuned(path, s)
+    assert a.ms_tune > 0.0 and len(lines) == 2
+    b, lines = tuned(path, s)
+    assert b.ms_tune == 0.0 and len(lines) == 2 and b.tile_shape == a.tile_shape
