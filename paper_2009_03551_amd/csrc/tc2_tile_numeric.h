@@ -58,6 +58,11 @@ static_assert((1 << (32 - KLQ_BITS)) >= KLMAX_ALL && (1 << KLQ_BITS) >= MAX_SYS_
 // longer than its waits, and two blocks of 8 waves fill each other's gaps (1728
 // atoms in three directions: 677 ms, with 16 waves 769).
 constexpr int waves(bool fine, int D) { return fine || D >= 2 ? 8 : 16; }
+// With the network or logging, updates of few sub-tiles run in parts only where a
+// sub-tile otherwise takes several parts one after another (FP32 and bfloat16
+// values, two or three directions: 343 atoms in three, FP32, logging: 105 ms per
+// solve whole, 90 in parts; 600-atom chain 27.6, 19.0).
+constexpr bool learn_parts(int D, int SP, int TQ) { return D >= 2 && SP * TQ > 16; }
 
 // the 1 + D block norms of an entry
 template <int D>
@@ -213,7 +218,7 @@ __device__ __forceinline__ void tile_numeric() {
   // block takes the next sub-tile from an atomic counter until all are done;
   // the sub-tile count then comes from the device (tile_rp[nc]).
   int total = (k->n_tiles_dev ? *k->n_tiles_dev : k->n_tiles) * SUBS;
-  if (!LEARN && (total <= k->fine_subs) != FINE) return;  // the other split's
+  if ((!LEARN || learn_parts(D, SP, TQ)) && (total <= k->fine_subs) != FINE) return;  // the other split's
   if constexpr (FINE) total *= PARTS;
   for (int it = 0;; ++it) {
     k = kargs();
@@ -937,12 +942,16 @@ __global__ __launch_bounds__(waves(false, D) * 64, 4) void k_tile_numeric(TileAr
   tile_numeric<T, D, SP, TQ, BF, W, FK, WS, false, false>();
 }
 template <typename T, int D, int SP, int TQ, bool BF, bool W, bool FK, int WS>
+__global__ __launch_bounds__(waves(true, D) * 64, 4) void k_tile_fine(TileArgs) {
+  tile_numeric<T, D, SP, TQ, BF, W, FK, WS, false, true>();
+}
+template <typename T, int D, int SP, int TQ, bool BF, bool W, bool FK, int WS>
 __global__ __launch_bounds__(waves(false, D) * 64, 4) void k_tile_learn(TileArgs) {
   tile_numeric<T, D, SP, TQ, BF, W, FK, WS, true, false>();
 }
 template <typename T, int D, int SP, int TQ, bool BF, bool W, bool FK, int WS>
-__global__ __launch_bounds__(waves(true, D) * 64, 4) void k_tile_fine(TileArgs) {
-  tile_numeric<T, D, SP, TQ, BF, W, FK, WS, false, true>();
+__global__ __launch_bounds__(waves(true, D) * 64, 4) void k_tile_learn_fine(TileArgs) {
+  tile_numeric<T, D, SP, TQ, BF, W, FK, WS, true, true>();
 }
 
 // Trace sums of the sub-tiles from the rows of their outputs: 16 lanes per sub-tile.
@@ -993,12 +1002,21 @@ static void tile_go_w(hipStream_t st, const TileArgs& a) {
     }
     hipLaunchKernelGGL(kernel, dim3(G), dim3(threads), 0, st, a);
   };
-  if (learn) return go(k_tile_learn<T, D, SP, TQ, BF, W, FK, WS>, subs, waves(false, D) * 64);
+  if (learn && !learn_parts(D, SP, TQ))
+    return go(k_tile_learn<T, D, SP, TQ, BF, W, FK, WS>, subs, waves(false, D) * 64);
+  auto whole = k_tile_numeric<T, D, SP, TQ, BF, W, FK, WS>;
+  auto fine = k_tile_fine<T, D, SP, TQ, BF, W, FK, WS>;
+  if constexpr (learn_parts(D, SP, TQ)) {
+    if (learn) {
+      whole = k_tile_learn<T, D, SP, TQ, BF, W, FK, WS>;
+      fine = k_tile_learn_fine<T, D, SP, TQ, BF, W, FK, WS>;
+    }
+  }
   // a.n_tiles bounds the count on the device, where there is one
-  if (subs > (unsigned)a.fine_subs) go(k_tile_numeric<T, D, SP, TQ, BF, W, FK, WS>, subs, waves(false, D) * 64);
+  if (subs > (unsigned)a.fine_subs) go(whole, subs, waves(false, D) * 64);
   if (a.fine_subs > 0 && (subs <= (unsigned)a.fine_subs || a.n_tiles_dev)) {
     const unsigned few = std::min(subs, (unsigned)a.fine_subs);
-    go(k_tile_fine<T, D, SP, TQ, BF, W, FK, WS>, few * PARTS, waves(true, D) * 64);
+    go(fine, few * PARTS, waves(true, D) * 64);
     hipLaunchKernelGGL((k_sub_sums<SP * TQ, SUBS>), dim3((few + 15) / 16), dim3(256), 0, st, a,
                        a.waves_per_column == 1 ? SP : SP / WS);
   }

@@ -73,3 +73,39 @@ def test_shapes_timed_with_another_kernel_are_timed_again(tmp_path):
     assert a.ms_tune > 0.0 and len(lines) == 2
     b, lines = tuned(path, s)
     assert b.ms_tune == 0.0 and len(lines) == 2 and b.tile_shape == a.tile_shape
+
+
+FP32 = dict(precision="fp32", closing_fp64=2)
+KINDS = {"fp64": dict(), "fp32": FP32, "bf16": dict(precision="bf16", closing_fp64=2),
+         "fp32w": dict(FP32, wide=True, fp64_first=2),
+         "bf16w": dict(precision="bf16", wide=True, fp64_first=2, closing_fp64=2)}
+
+
+@pytest.mark.parametrize("kind", list(KINDS))
+@pytest.mark.parametrize("D", [0, 1, 2, 3])
+def test_learned_screen_in_parts_equals_whole_subtiles(knob, kind, D):
+    # the same features, logits and decisions, whichever workgroup computes an
+    # output: equal matrices and logs (samples in any order).  45 atoms: six
+    # clusters, the last one ragged
+    s = W.batch_systems(sizes=[45], n_dir=D, b=13 if D != 2 else 6)[0]
+    theta = np.zeros(T.MLP_PARAMS, dtype=np.float32)
+    theta[:] = np.random.default_rng(2).normal(0.0, 0.3, T.MLP_PARAMS)
+
+    def run():
+        a = T.solve(s, skip="mlp", mlp_weights=theta, mlp_threshold=0.5, mlp_bound_cap=2.0,
+                    **KINDS[kind])[0]
+        sv = T.Solver(s, skip="bound", log_capacity=200000, **KINDS[kind])
+        b = sv.run()[0]
+        x, y = sv.log()
+        sv.close()
+        order = np.lexsort(np.concatenate([x.T, y[None]]))
+        return a, b, x[order], y[order]
+
+    a0, b0, x0, y0 = run()
+    knob("TC2_TEST_FINE_SUBS", 0)
+    a1, b1, x1, y1 = run()
+    same(a0, a1)
+    same(b0, b1)
+    assert a0.mlp_skipped_blocks == a1.mlp_skipped_blocks
+    assert a0.screened_blocks == a1.screened_blocks and b0.screened_blocks == b1.screened_blocks
+    assert len(y0) > 0 and np.array_equal(x0, x1) and np.array_equal(y0, y1)
