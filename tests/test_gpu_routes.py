@@ -109,3 +109,78 @@ def test_learned_screen_in_parts_equals_whole_subtiles(knob, kind, D):
     assert a0.mlp_skipped_blocks == a1.mlp_skipped_blocks
     assert a0.screened_blocks == a1.screened_blocks and b0.screened_blocks == b1.screened_blocks
     assert len(y0) > 0 and np.array_equal(x0, x1) and np.array_equal(y0, y1)
+
+
+KIND_ID = {"fp64": 0, "fp32": 1, "bf16": 2, "fp32w": 3, "bf16w": 3}
+KIND_KEY = ("fp64", "fp32", "bf16", "fp32w")
+
+
+def instances():
+    """Kind, directions and shape of every instance of the tiled kernel."""
+    for kind in KINDS:
+        for D in range(4):
+            if kind in ("fp64", "fp32w", "bf16w") and D >= 2:
+                yield kind, D, "4x4"
+                continue
+            yield kind, D, "8x8"
+            if D in (1, 3):
+                yield kind, D, "4x8"
+            if D == 1 and kind != "bf16":
+                yield kind, D, "8x4"
+
+
+def forced(tmp_path, kind, D, b, shape):
+    """Options that set `shape` for the kind and 8x8 or 4x4 for the others."""
+    path = tmp_path / f"shapes_{kind}_{D}_{shape}"
+    lines = []
+    for k in KIND_KEY:
+        wide = k in ("fp64", "fp32w") and D >= 2
+        sh = shape if k == KIND_KEY[KIND_ID[kind]] else ("4x4" if wide else "8x8")
+        lines.append(json.dumps({"key": f"gfx950/{k}/D{D}/k{(b + 3) // 4}/s1", "shape": sh, "ms": {}}))
+    path.write_text("\n".join(lines) + "\n")
+    return dict(skip="bound", tune=True, tune_cache=str(path), **KINDS[kind])
+
+
+@pytest.mark.parametrize("b", [13, 9, 16])
+@pytest.mark.parametrize("kind,D,shape", list(instances()))
+def test_whole_subtiles_of_every_instance(knob, tmp_path, kind, D, shape, b):
+    # small systems run in parts, the same for every shape; larger ones take the
+    # instance of the shape, here forced: all results are those of the parts.
+    # The sums over a sub-tile's outputs follow its shape.
+    s = W.batch_systems(sizes=[29], n_dir=D, b=b)[0]
+    parts = T.solve(s, **dict(KINDS[kind], skip="bound"))[0]
+    knob("TC2_TEST_FINE_SUBS", 0)
+    whole = T.solve(s, **forced(tmp_path, kind, D, b, shape))[0]
+    assert whole.tile_shape[KIND_ID[kind]] == ("8x8", "4x8", "8x4", "4x4").index(shape)
+    assert whole.ms_tune == 0.0
+    for x, y in zip([parts.X0] + parts.X1, [whole.X0] + whole.X1):
+        assert np.array_equal(x.row_ptr, y.row_ptr) and np.array_equal(x.col, y.col)
+        assert np.array_equal(x.val, y.val)
+    assert parts.branches == whole.branches and parts.iters == whole.iters
+    assert parts.executed_flops == whole.executed_flops
+    assert parts.screened_blocks == whole.screened_blocks
+    assert whole.alpha == pytest.approx(parts.alpha, rel=1e-12)
+    # panel passes of 8 columns, and every product issued: equal matrices again
+    for name, value in (("TC2_TEST_KL_CHUNK", 8), ("TC2_TEST_NO_ZERO_SKIP", 1)):
+        knob(name, value)
+        other = T.solve(s, **forced(tmp_path, kind, D, b, shape))[0]
+        for x, y in zip([other.X0] + other.X1, [whole.X0] + whole.X1):
+            assert np.array_equal(x.row_ptr, y.row_ptr) and np.array_equal(x.col, y.col)
+            assert np.array_equal(x.val, y.val)
+
+
+@pytest.mark.parametrize("kind,D", [("fp64", 0), ("fp64", 1), ("fp64", 2), ("fp64", 3), ("fp32w", 1),
+                                    ("fp32w", 3), ("bf16w", 2)])
+def test_trace_groups_of_whole_subtiles(knob, kind, D):
+    # the traces of a whole sub-tile are summed in the groups that the parts
+    # use, or (waves per column 1) by column of the sub-tile
+    s = W.batch_systems(sizes=[61], n_dir=D, b=13)[0]
+    a = T.solve(s, **KINDS[kind])[0]
+    knob("TC2_TEST_FINE_SUBS", 0)
+    b = T.solve(s, **KINDS[kind])[0]
+    same(a, b)
+    knob("TC2_TEST_WAVES_PER_COLUMN", 1)
+    c = T.solve(s, **KINDS[kind])[0]
+    assert c.alpha == pytest.approx(b.alpha, rel=1e-12)
+    for x, y in zip([c.X0] + c.X1, [b.X0] + b.X1):
+        assert np.array_equal(x.val, y.val)
