@@ -118,16 +118,21 @@ __device__ __forceinline__ int wave_scan(int v) {
 // barrier that lets the block be read.  In assembly, because behind the builtin
 // the compiler waits for every copy in flight before it reads any LDS address,
 // which would end the overlap of the copies of one stage with the products of
-// another.  Nothing else here uses m0.  The s_nop covers an SGPR of src written
-// by a readlane just before.
+// another.  m0 is named as clobbered so that no use of it by the compiler can
+// stand across the copy (the compiler warns that the register is reserved, that
+// is, not kept across assembly, as is meant).  The s_nop covers an SGPR of src
+// written by a readlane just before.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void lds_copy(const char* src, unsigned dst, int off, int n) {
   if (off < n)
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :: "s"(dst), "v"(off), "s"(src) : "memory");
+                 :: "s"(dst), "v"(off), "s"(src) : "memory", "m0");
   if (n > 1024 && off + 1024 < n)
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2 offset:1024"
-                 :: "s"(dst), "v"(off), "s"(src) : "memory");
+                 :: "s"(dst), "v"(off), "s"(src) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 
 // the trace sums of a sub-tile from those of its outputs (NQ apart): ng groups of go
 __device__ __forceinline__ double sub_sum(const double* row, int ng, int go) {
