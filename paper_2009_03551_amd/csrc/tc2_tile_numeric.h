@@ -177,8 +177,7 @@ __device__ __forceinline__ void tile_numeric() {
   constexpr int NO = PS * PT / NWB;                       // outputs per wave
   constexpr int PARTS = NOUT / (PS * PT);
   constexpr int NE = PS + PT;                             // entries per column
-  constexpr int NX = (NE + NWB - 1) / NWB;                // entries per column copied by a wave
-  constexpr int CW = NE < NWB ? NWB / NE : 1;             // or waves that share one
+  static_assert(NE <= NWB, "wave x copies entry x of a column");
   constexpr int NM = 1 + D;                               // matrices
   constexpr unsigned MM = (1u << NM) - 1u;
   constexpr int BPE = NM <= 2 ? 2 : 4;                    // plan bits per entry
@@ -654,13 +653,13 @@ __device__ __forceinline__ void tile_numeric() {
       //  word[o]: needed blocks before the column (11 bits) << 18 | offsets of the
       //    blocks of X_IK and X_JK within the column (5 + 5 bits) << 8 | the
       //    matrices staged of X_JK, X_IK (4 + 4 bits); 0: no product
-      //  ce[i], cw[i]: entry this wave copies, and its first block (chunk) << 4 |
-      //    matrices needed
+      //  ce, cw: entry this wave copies (waves from NE on: none), and its first
+      //    block (chunk) << 4 | matrices needed
       struct Plan {
         int send;
         unsigned word[NO];
-        int ce[NX];
-        unsigned cw[NX];
+        int ce;
+        unsigned cw;
       };
       auto plan_round = [&](int base, int r0) {
         KArgs k = kargs();
@@ -716,8 +715,8 @@ __device__ __forceinline__ void tile_numeric() {
           if (lane < PS * PT) atomicAdd(&s_np[lane], cnt);
           // needed matrices: X0 with any partner's nonzero matrix, X1_d with a
           // partner's nonzero X0
+          static_assert(PS * BPE <= 16 && PT * BPE <= 16, "bits of a side");
           auto fold = [](unsigned u) {
-            if (PT * BPE > 16) u |= u >> 16;
             u |= u >> 8;
             u |= u >> 4;
             if (BPE == 2) u |= u >> 2;
@@ -740,15 +739,11 @@ __device__ __forceinline__ void tile_numeric() {
         KArgs k = kargs();
         const unsigned w = s_need[c0 - r0 + lane];
         p.send = wave_scan(__popc(w));
-        int at_e[NX];
         const unsigned kk = kl[min(c0 + lane, nm - 1)];
-#pragma unroll
-        for (int i = 0; i < NX; ++i) {
-          const int x = CW > 1 ? wave % NE : wave + i * NWB;
-          const size_t row = x < PS ? (size_t)(base + (int)(kk >> KLQ_BITS)) * CS + ph + s0 + x
-                                    : (size_t)(pq0 + (int)(kk & ((1u << KLQ_BITS) - 1u))) * CS + qh + t0 + min(x - PS, PT - 1);
-          at_e[i] = k->panel_e[row];
-        }
+        const int x = wave;
+        const size_t row = x < PS ? (size_t)(base + (int)(kk >> KLQ_BITS)) * CS + ph + s0 + x
+                                  : (size_t)(pq0 + (int)(kk & ((1u << KLQ_BITS) - 1u))) * CS + qh + t0 + min(x - PS, PT - 1);
+        const int at_e = k->panel_e[row];
         const unsigned first = (unsigned)(p.send - __popc(w));
         auto below = [&](int x) { return (unsigned)__popc(w & ((1u << (BPE * x)) - 1u)); };
 #pragma unroll
@@ -760,40 +755,28 @@ __device__ __forceinline__ void tile_numeric() {
                           ? (first << 18) | (below(to) << 13) | (below(so) << 8) | (nb << 4) | na
                           : 0u;
         }
-#pragma unroll
-        for (int i = 0; i < NX; ++i) {
-          const int x = CW > 1 ? wave % NE : wave + i * NWB;
-          p.cw[i] = x < NE && wave < NE * (CW > 1 ? CW : NX) ? ((first + below(x)) << 4) | ((w >> (BPE * x)) & EM) : 0u;
-          p.ce[i] = at_e[i];
-          asm volatile("" : "+v"(p.ce[i]));  // loaded before the copies below (the compiler would wait for those too)
-        }
+        p.cw = x < NE ? ((first + below(x)) << 4) | ((w >> (BPE * x)) & EM) : 0u;
+        p.ce = at_e;
+        asm volatile("" : "+v"(p.ce));  // loaded before the copies below (the compiler would wait for those too)
       };
 
       // f(slot offset, matrix, entry) for the blocks that this wave copies of the
       // columns [c0, c1) of plan p, block n of the chunk in slot n + shift
       // (modulo the ring)
       auto each_block = [&](const Plan& p, int c0, int c1, int shift, auto&& f) {
-#pragma unroll
-        for (int i = 0; i < NX; ++i) {
-          unsigned long long todo = __ballot(lane >= c0 && lane < c1 && (p.cw[i] & 15u));
-          while (todo) {
-            const int l = __ffsll((long long)todo) - 1;
-            todo &= todo - 1;
-            const int e = __builtin_amdgcn_readlane(p.ce[i], l);
-            const unsigned w = (unsigned)__builtin_amdgcn_readlane((int)p.cw[i], l);
-            unsigned n = w & 15u;
-            int dst = wrap(((int)(w >> 4) + shift) * sbytes);
-            int turn = CW > 1 ? wave / NE : 0;
-            while (n) {
-              const int m = __ffs((int)n) - 1;
-              n &= n - 1;
-              if (CW == 1 || turn == 0) {
-                f(dst, m, e);
-                turn = CW;
-              }
-              --turn;
-              dst = wrap(dst + sbytes);
-            }
+        unsigned long long todo = __ballot(lane >= c0 && lane < c1 && (p.cw & 15u));
+        while (todo) {
+          const int l = __ffsll((long long)todo) - 1;
+          todo &= todo - 1;
+          const int e = __builtin_amdgcn_readlane(p.ce, l);
+          const unsigned w = (unsigned)__builtin_amdgcn_readlane((int)p.cw, l);
+          unsigned n = w & 15u;
+          int dst = wrap(((int)(w >> 4) + shift) * sbytes);
+          while (n) {
+            const int m = __ffs((int)n) - 1;
+            n &= n - 1;
+            f(dst, m, e);
+            dst = wrap(dst + sbytes);
           }
         }
       };
