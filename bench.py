@@ -36,10 +36,24 @@ HBM_PEAK_GBS = 8000.0
 SHAPES = ((8, 8), (4, 8), (8, 4), (4, 4))   # sub-tile shape id -> (rows, columns)
 
 
-def kernel_name(kernel: str, kind: int, D: int, shape: int, b: int, split: bool = False) -> str:
+FINE_SUBS = 2048   # sub-tiles up to which an update runs in parts (csrc/tc2_internal.h)
+
+
+def runs_in_parts(atoms, shape: int) -> bool:
+    """Whether every update of systems of `atoms` atoms runs in parts of
+    sub-tiles: all pairs of their clusters of 8 atoms make at most FINE_SUBS."""
+    sp, tq = SHAPES[max(shape, 0)]
+    clusters = [(n + 7) // 8 for n in atoms]
+    return sum(m * (m + 1) // 2 for m in clusters) * (8 // sp) * (8 // tq) <= FINE_SUBS
+
+
+def kernel_name(kernel: str, kind: int, D: int, shape: int, b: int, split: bool = False,
+                parts: bool = False, learn: bool = False) -> str:
     """Template instance of the numeric kernel of one kind (FP64, FP32, BF16
     operands, FP32 with FP64 sums; with `split`, the FP64-sum kind runs the
-    three-way bfloat16 split), as rocprofv3 names it."""
+    three-way bfloat16 split), as rocprofv3 names it.  `parts`: small updates
+    (runs_in_parts); `learn`: with the skip network or feature logging, in parts
+    only where a sub-tile is more than 16 outputs of two or three directions."""
     T = "double" if kind == 0 else "float"
     if kernel == "block":
         return f"k_numeric<{T}, {D}>"
@@ -55,12 +69,18 @@ def kernel_name(kernel: str, kind: int, D: int, shape: int, b: int, split: bool 
     elif (kind == 0 or (kind == 3 and not split)) and D <= 1 and (sp, tq) == (8, 8):
         ws = 2
     tf = lambda v: "true" if v else "false"
-    return (f"k_tile_numeric<{T}, {D}, {sp}, {tq}, {tf(bf)}, {tf(kind == 3)}, {tf(full_k)}, "
+    if learn:
+        name = "k_tile_learn_fine" if parts and D >= 2 and sp * tq > 16 else "k_tile_learn"
+    else:
+        name = "k_tile_fine" if parts else "k_tile_numeric"
+    return (f"{name}<{T}, {D}, {sp}, {tq}, {tf(bf)}, {tf(kind == 3)}, {tf(full_k)}, "
             f"{ws}>")
 
-KERNEL_SOURCES = ("paper_2009_03551_amd/csrc/tc2_tile.hip",
+
+KERNEL_SOURCES = ("paper_2009_03551_amd/csrc/tc2_tile.hip", "paper_2009_03551_amd/csrc/tc2_tile.h",
                   "paper_2009_03551_amd/csrc/tc2_tile_numeric.h", "paper_2009_03551_amd/csrc/tc2_device.h",
-                  "paper_2009_03551_amd/csrc/tc2_internal.h", "paper_2009_03551_amd/csrc/tc2_kernels.hip")
+                  "paper_2009_03551_amd/csrc/tc2_internal.h", "paper_2009_03551_amd/csrc/tc2_kernels.hip",
+                  "paper_2009_03551_amd/csrc/tc2_runtime.hip")
 
 
 def log(msg: str) -> None:
@@ -759,7 +779,9 @@ def main() -> int:
     pm = measured_peaks() or {}
     pk_meas = None if split else pm.get({0: "gemm_fp64_tflops", 1: "gemm_fp32_tflops",
                                          3: "gemm_fp32_tflops"}.get(dom, ""))
-    kname = kernel_name(args.kernel, dom, D, r.tile_shape[dom], sysm.H.b, split)
+    kname = kernel_name(args.kernel, dom, D, r.tile_shape[dom], sysm.H.b, split,
+                        parts=all(runs_in_parts([sy.H.nb for sy in un], r.tile_shape[dom]) for un in units),
+                        learn=args.skip == "mlp")
     traffic = measured_traffic(kname.split("<")[0], args.workload,
                                ("fp64", "fp32", "bf16", "fp32w")[dom])
     plain = refs[0][0] if refs and refs[0][0] == "plain FP64 GPU path" else None

@@ -65,3 +65,22 @@ def test_pack_units_keeps_order_and_bounds():
     assert [[s.H.nb for s in u] for u in units] == [[5, 7], [3], [20], [2, 2], [9]]
     assert all(sum(s.H.nb for s in u) <= 12 or len(u) == 1 for u in units)
     assert W.pack_units([], 12) == []
+
+
+def test_kernel_names_of_small_and_learned_updates():
+    with open(os.path.join(ROOT, "paper_2009_03551_amd", "csrc", "tc2_internal.h")) as f:
+        assert int(re.search(r"FINE_SUBS = (\d+);", f.read()).group(1)) == bench.FINE_SUBS
+    # 64 atoms: 36 pairs of clusters; 1000: 7875; the sub-tile of 16 outputs has
+    # four per pair (31 clusters: 496, 32: 528)
+    assert bench.runs_in_parts([64], 1) and not bench.runs_in_parts([1000], 0)
+    assert bench.runs_in_parts([248], 3) and not bench.runs_in_parts([256], 3)
+    assert not bench.runs_in_parts([248, 64], 3)
+    whole = bench.kernel_name("tile", 0, 1, 1, 8)
+    assert whole.startswith("k_tile_numeric<double, 1, 4, 8,")
+    assert bench.kernel_name("tile", 0, 1, 1, 8, parts=True) == whole.replace("numeric", "fine")
+    assert bench.kernel_name("tile", 0, 1, 1, 8, parts=True, learn=True) == whole.replace("numeric", "learn")
+    assert bench.kernel_name("tile", 1, 3, 0, 13, parts=True, learn=True).startswith("k_tile_learn_fine<float, 3, 8, 8,")
+    assert bench.kernel_name("block", 0, 2, -1, 8, parts=True) == "k_numeric<double, 2>"
+    # what decides the instance decides whether recorded figures are current
+    for f in ("tc2_tile.h", "tc2_tile_numeric.h", "tc2_runtime.hip"):
+        assert any(k.endswith("/" + f) for k in bench.KERNEL_SOURCES)
