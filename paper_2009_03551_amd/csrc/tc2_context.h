@@ -315,7 +315,7 @@ struct tc2_ctx {
   size_t panel_bound = tc2::VM_MIN;  // panel buffers counted, not bounded, from this size on
   long long test_stage_cap = 0;
   int test_no_zero_skip = 0;      // issue every product (masks not passed to the kernel)
-  int test_waves_per_column = 0;  // 1: trace sums grouped by sub-tile column in every numeric kernel
+  int test_column_sums = 0;       // 1: trace sums grouped by column of the sub-tile only
   std::vector<int> h_active;      // host copy of the active flags
   // clusters
   int nc = 0, max_sys_clusters = 0;

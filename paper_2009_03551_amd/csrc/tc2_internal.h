@@ -116,14 +116,15 @@ struct NumArgs {
   int* rowcnt;              // nb: blocks kept per row (zeroed)
 };
 
-// Cluster row panels: for cluster P the sorted union of the columns K of its
-// atoms' rows, with the entry index of (I_s, K) for each member s (-1 absent).
-struct ClearArgs {        // integers set to 0
+// Integers set to 0 in one launch: n[k] from p[k] on.
+struct ClearArgs {
   static constexpr int N = 6;
   int* p[N];
   long long n[N];
 };
 
+// Cluster row panels: for cluster P the sorted union of the columns K of its
+// atoms' rows, with the entry index of (I_s, K) for each member s (-1 absent).
 struct PanelArgs {
   int nc;
   const int* rp;
@@ -182,7 +183,7 @@ struct TileArgs {
   int kl_chunk;           // 0: default panel pass length
   int b;                  // block size
   int ksteps;             // ceil(b / 4): K-steps of 4 in the padded tile
-  int waves_per_column;   // 1: trace sums grouped by column of the sub-tile only (tests compare)
+  int column_sums;        // 1: trace sums grouped by column of the sub-tile only (tests compare)
   int n_tiles;
   const int* rp;
   const int* ci;
@@ -308,11 +309,19 @@ int tile_subs(int shape);  // sub-tiles per tile of 8 x 8 output blocks
 // Updates of at most this many sub-tiles run in parts of 8 outputs (one per
 // wave), others a sub-tile per workgroup.  512 workgroups of parts fit on the
 // chip: with few sub-tiles the parts fill compute units that would idle or wait
-// for the longest sub-tile (64-atom chain, 72 sub-tiles: 183 -> 70 us per
-// update; 100 atoms in three directions, 364: 723 -> 633; 1024-atom chain: 24.4
-// ms per solve with a limit of 1024, 23.7 with 2048), with many, operands shared
-// by fewer outputs cost more than the balance gives (343 atoms, 3784 sub-tiles:
-// 6 % slower in parts; batch of five, limit 4096: 8 %).
+// for the longest sub-tile, with many, operands shared by fewer outputs cost
+// more than the balance gives.  Measured, ms per solve with limits of 2048, 1024
+// and 0 (lattices of 13 x 13 blocks, chains of 8 x 8):
+//   no direction   216 atoms   12.0  12.0  13.3     512 atoms   42.1  42.9  43.0
+//   one            64-chain     3.8   3.8   4.9     216 atoms   32.2  32.2  37.0
+//                  420 atoms   98.4  96.8  96.7     512 atoms  130.8 132.3 132.4
+//                  1024-chain  14.8  15.1  17.9     2000-chain  26.4  29.1  29.0
+//   two            216 atoms   45.7  47.1  47.1     512-chain   10.8  11.6  11.5
+//   three          125 atoms   22.6  22.5  21.5     180 atoms   45.5  43.4  43.3
+//                  343 atoms  137.0 137.2 136.6     512-chain   12.2  13.4  13.3
+// (a 4 x 4 sub-tile is two parts and an 8 x 8 one eight, so that a limit in parts
+// would lie elsewhere for each; beyond the limit, 343 atoms in three directions,
+// 3784 sub-tiles: 6 % slower in parts; batch of five, limit 4096: 8 %).
 constexpr int FINE_SUBS = 2048;
 // bytes of the trace sums per output of those parts
 inline size_t tile_rows_bytes(long long n_tiles) {

@@ -178,8 +178,8 @@ __global__ __launch_bounds__(256) void k_symbolic(int pass, SymArgs a) {
 }
 
 // ------------------------------------------------------------------ scans
-// Exclusive scan of n ints into out[0..n] (out[n] = total), single block.
-// Exclusive sums of in[0 .. n) by one block, four values per thread at a time.
+// Exclusive sums of in[0 .. n) into out[0 .. n], out[n] and *total the sum of
+// all, by one block, four values per thread at a time.
 __global__ __launch_bounds__(1024) void k_scan(int n, const int* in, int* out, int* total) {
   __shared__ int sh[2][16];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;

@@ -372,7 +372,7 @@ static tc2_status setup_impl(const tc2_problem* probs, int32_t np, const tc2_opt
   if (const char* v = getenv("TC2_TEST_PANEL_BOUND")) ctx->panel_bound = (size_t)std::max(0LL, atoll(v));
   if (const char* v = getenv("TC2_TEST_STAGE_CAP")) ctx->test_stage_cap = std::max(0LL, atoll(v));
   if (const char* v = getenv("TC2_TEST_NO_ZERO_SKIP")) ctx->test_no_zero_skip = atoi(v) != 0;
-  if (const char* v = getenv("TC2_TEST_WAVES_PER_COLUMN")) ctx->test_waves_per_column = atoi(v);
+  if (const char* v = getenv("TC2_TEST_WAVES_PER_COLUMN")) ctx->test_column_sums = atoi(v) == 1;
   tc2_status st = TC2_OK;
   auto fail = [&](tc2_status s) {
     tc2_free(ctx);
@@ -530,11 +530,13 @@ static tc2_status setup_impl(const tc2_problem* probs, int32_t np, const tc2_opt
       ctx->tile_bound += m * (m + 1) / 2;
     }
     if (ctx->tune) tune_load(ctx);
-    // with fewer cluster pairs than compute units, one workgroup per pair
-    // leaves most units idle and each runs the whole column loop of its
-    // pair: the FP64 kind, 8x8 by default, then takes the 4x8 sub-tile (two
-    // workgroups per pair; on a 64-atom chain the products took 0.155 ms per
-    // update instead of 0.216), unless a tuned shape was loaded
+    // with fewer cluster pairs than compute units, one workgroup per pair leaves
+    // most units idle and each runs the whole column loop of its pair: the FP64
+    // kind, 8x8 by default, then takes the 4x8 sub-tile, two workgroups per pair,
+    // unless a tuned shape was loaded.  It decides the kernel with the skip network
+    // or logging, which takes whole sub-tiles (64-atom chain, network: 10.6 ms per
+    // solve with 8x8, 7.7 with 4x8; 125 atoms, logging: 23.9, 18.2); without them
+    // such updates run in parts, the same for both (4.0 ms).
     int n_cu = 0;
     if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess) {
       (void)hipGetLastError();
@@ -651,7 +653,7 @@ tc2_status measure(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal) {
 }
 
 // Zero the per-system nominal counters and count this update's full-product
-// triples on the pattern rp (stream work; also recorded into update graphs).
+// triples on the pattern rp (updates without panels, which count them on the way).
 tc2_status count_nominal(tc2_ctx* ctx, hipStream_t st, const int* rp) {
   launch_fill_int(st, ctx->nominal.as<int>(), 0, 2LL * ctx->nsys);
   const unsigned g = (unsigned)std::min(65535, (ctx->nb + 255) / 256);
@@ -873,7 +875,7 @@ tc2_status step(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
     ta.wide = wide_now;
     ta.skip = ctx->skip_now;
     ta.xmask = ctx->test_no_zero_skip ? nullptr : ctx->mask[c].as<unsigned char>();
-    ta.waves_per_column = ctx->test_waves_per_column;
+    ta.column_sums = ctx->test_column_sums;
     ta.bn = screen ? ctx->bn.as<float>() : nullptr;
     ta.screened = screen ? ctx->screened.as<unsigned long long>() : nullptr;
     ta.mlp_skipped = screen ? ctx->screened.as<unsigned long long>() + 1 : nullptr;
@@ -1361,7 +1363,7 @@ int step_graph(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
       ta.shape = shape;
       ta.skip = ctx->skip_now;
       ta.xmask = ctx->test_no_zero_skip ? nullptr : ctx->mask[c].as<unsigned char>();
-      ta.waves_per_column = ctx->test_waves_per_column;
+      ta.column_sums = ctx->test_column_sums;
       ta.bn = screen ? ctx->bn.as<float>() : nullptr;
       ta.screened = screen ? ctx->screened.as<unsigned long long>() : nullptr;
       ta.mlp_skipped = screen ? ctx->screened.as<unsigned long long>() + 1 : nullptr;

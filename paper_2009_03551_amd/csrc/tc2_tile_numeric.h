@@ -165,7 +165,7 @@ __device__ __forceinline__ void tile_numeric() {
   constexpr int NOUT = SP * TQ;                           // outputs of the sub-tile
   KArgs k = kargs();
   // groups of the trace sums and outputs per group (tests compare with WS = 1)
-  const int GO = k->waves_per_column == 1 ? SP : SP / WS, NG = NOUT / GO;
+  const int GO = k->column_sums ? SP : SP / WS, NG = NOUT / GO;
   static_assert(SP % WS == 0, "rows of the sub-tile split evenly over its groups");
   // place of output (row r, column q) of the sub-tile in that order
   auto sum_row = [&](int r, int q) { return ((r / GO) * TQ + (q + TQ - r % TQ) % TQ) * GO + r % GO; };
@@ -1006,7 +1006,7 @@ static void tile_go_w(hipStream_t st, const TileArgs& a) {
     const unsigned few = std::min(subs, (unsigned)a.fine_subs);
     go(fine, few * PARTS, waves(true, D) * 64);
     hipLaunchKernelGGL((k_sub_sums<SP * TQ, SUBS>), dim3((few + 15) / 16), dim3(256), 0, st, a,
-                       a.waves_per_column == 1 ? SP : SP / WS);
+                       a.column_sums ? SP : SP / WS);
   }
 }
 
