@@ -30,6 +30,19 @@ void vm_release(DBuf& b);                  // chunks back to the pool, range fre
 void pool_trim();                          // pooled chunks of the device to the GPU driver
 bool device_wait();                        // for all work of the device; captures go on
 
+// A stream of the current device for the copies of a set-up or one graph capture,
+// kept for the next one afterwards (broken: not kept); st is null when none can
+// be made.  The work on it has ended when it is given back.
+struct ServiceStream {
+  hipStream_t st = nullptr;
+  int dev = 0;
+  bool broken = false;
+  ServiceStream();
+  ~ServiceStream();
+  ServiceStream(const ServiceStream&) = delete;
+  ServiceStream& operator=(const ServiceStream&) = delete;
+};
+
 struct DBuf {
   void* p = nullptr;
   size_t cap = 0;
@@ -324,7 +337,7 @@ struct tc2_ctx {
   // graph-captured updates (tiled kernel): one executable graph per iterate
   // buffer, valid while the key (buffers, sizes, kind, shape) is unchanged
   int graph = 0;                  // option: capture updates in hipGraphs
-  hipStream_t cap = nullptr;      // captures update graphs (launched on the run's stream)
+  hipStream_t up = nullptr;       // copies of the set-up
   bool graph_ok = true;           // false after a capture the runtime refused
   hipGraphExec_t gexec[2] = {nullptr, nullptr};
   hipGraphExec_t gexec_post[2] = {nullptr, nullptr};  // profiling: the part after the products

@@ -83,7 +83,7 @@ template <typename T>
 tc2_status upload(tc2_ctx* ctx, DBuf& d, const std::vector<T>& h) {
   HIPCHK(d.reserve(h.size() * sizeof(T)));
   if (!h.empty())
-    HIPCHK(hipMemcpyWithStream(d.p, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice, ctx->own));
+    HIPCHK(hipMemcpyWithStream(d.p, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice, ctx->up));
   return TC2_OK;
 }
 
@@ -177,7 +177,6 @@ void tc2_free(tc2_ctx* ctx) {
   if (!ctx) return;
   (void)hipSetDevice(ctx->device);
   if (ctx->own) (void)hipStreamDestroy(ctx->own);
-  if (ctx->cap) (void)hipStreamDestroy(ctx->cap);
   for (hipEvent_t& e : ctx->pev)
     if (e) (void)hipEventDestroy(e);
   for (hipGraphExec_t& g : ctx->gexec)
@@ -379,6 +378,9 @@ static tc2_status setup_impl(const tc2_problem* probs, int32_t np, const tc2_opt
     return s;
   };
   if (hipStreamCreateWithFlags(&ctx->own, hipStreamNonBlocking) != hipSuccess) return fail(TC2_EDEVICE);
+  const ServiceStream up;
+  if (!up.st) return fail(TC2_EDEVICE);
+  ctx->up = up.st;
   if (ctx->profile)
     for (hipEvent_t& e : ctx->pev)
       if (hipEventCreate(&e) != hipSuccess) return fail(TC2_EDEVICE);
@@ -576,7 +578,8 @@ static tc2_status setup_impl(const tc2_problem* probs, int32_t np, const tc2_opt
   }
   if (ctx->rowlo.reserve((size_t)ctx->nb * b * 8) || ctx->rowhi.reserve((size_t)ctx->nb * b * 8))
     return fail(TC2_ENOMEM);
-  if (hipStreamSynchronize(ctx->own) != hipSuccess) return fail(TC2_EDEVICE);
+  if (hipStreamSynchronize(up.st) != hipSuccess) return fail(TC2_EDEVICE);
+  ctx->up = nullptr;
   *out = ctx;
   return TC2_OK;
 }
@@ -1442,32 +1445,31 @@ int step_graph(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
     };
     // Capture of a part sequence into an executable graph; false if refused.  On
     // a stream of its own: a device-wide wait by another thread ends the capture,
-    // and its stream then takes no more work (so the capture is tried again on a
-    // new one), while the caller's stream goes on.
+    // and its stream then takes no more work (so the capture is tried again on
+    // another one), while the caller's stream goes on.
     auto capture_once = [&](hipGraphExec_t* out, bool with_pre, bool with_num, bool with_post) {
-      if (!ctx->cap && hipStreamCreateWithFlags(&ctx->cap, hipStreamNonBlocking) != hipSuccess) {
-        (void)hipGetLastError();
-        ctx->cap = nullptr;
-        return false;
-      }
-      if (hipStreamBeginCapture(ctx->cap, hipStreamCaptureModeThreadLocal) != hipSuccess) {
+      ServiceStream cap;
+      if (!cap.st) return false;
+      cap.broken = true;
+      if (hipStreamBeginCapture(cap.st, hipStreamCaptureModeThreadLocal) != hipSuccess) {
         (void)hipGetLastError();
         return false;
       }
       bool ok = true;
-      rs = ctx->cap;
+      rs = cap.st;
       if (with_pre) rec_pre();
       if (with_num) ok = rec_num();
       if (with_post) rec_post();
       rs = st;
       if (hipGetLastError() != hipSuccess) ok = false;
       hipGraph_t graph = nullptr;
-      const hipError_t ee = hipStreamEndCapture(ctx->cap, &graph);
+      const hipError_t ee = hipStreamEndCapture(cap.st, &graph);
       if (ee != hipSuccess || !ok || !graph) {
         if (graph) (void)hipGraphDestroy(graph);
         (void)hipGetLastError();
         return false;
       }
+      cap.broken = false;
       const hipError_t ie = hipGraphInstantiate(out, graph, nullptr, nullptr, 0);
       (void)hipGraphDestroy(graph);
       if (ie != hipSuccess) {
@@ -1478,12 +1480,8 @@ int step_graph(tc2_ctx* ctx, hipStream_t st, std::vector<double>& scal,
       return true;
     };
     auto capture = [&](hipGraphExec_t* out, bool with_pre, bool with_num, bool with_post) {
-      for (int k = 0; k < 3; ++k) {
+      for (int k = 0; k < 3; ++k)
         if (capture_once(out, with_pre, with_num, with_post)) return true;
-        if (ctx->cap) (void)hipStreamDestroy(ctx->cap);
-        ctx->cap = nullptr;
-        (void)hipGetLastError();
-      }
       return false;
     };
     // one graph for the whole update; when profiling, the products run as a

@@ -35,6 +35,8 @@ std::map<uintptr_t, size_t> g_reserved;      // virtual ranges
 std::map<uintptr_t, uint64_t> g_mapped;      // address -> chunk
 std::map<uint64_t, size_t> g_chunk;          // chunk -> bytes
 uint64_t g_next_chunk = 1;
+std::set<hipStream_t> g_streams_made;
+uintptr_t g_next_stream = 0;
 std::atomic<int> g_stream_waits{0}, g_device_waits{0};
 std::function<void(void*)> g_on_unmap;       // before a mapping is taken away
 std::atomic<bool> g_busy{false};             // work in flight: no buffer may be handed on
@@ -60,6 +62,16 @@ hipError_t hipDeviceSynchronize() {
   return ++g_device_waits, hipSuccess;
 }
 hipError_t hipStreamSynchronize(hipStream_t) { return ++g_stream_waits, hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
+  std::lock_guard<std::mutex> g(g_m);
+  g_streams_made.insert(*s = (hipStream_t)(++g_next_stream * 16));
+  return hipSuccess;
+}
+hipError_t hipStreamDestroy(hipStream_t s) {
+  std::lock_guard<std::mutex> g(g_m);
+  check(g_streams_made.erase(s) == 1, "a stream destroyed twice");
+  return hipSuccess;
+}
 hipError_t hipDeviceTotalMem(size_t* n, hipDevice_t) { return *n = g_capacity, hipSuccess; }
 
 hipError_t hipMalloc(void** p, size_t n) {
@@ -277,12 +289,54 @@ void release_beside_capture() {
   check(!g_busy, "a buffer handed on with work in flight, memory full");
 }
 
+// Streams pass from one call to the next, are never two calls' at once, and are
+// bounded and given back.
+void service_streams() {
+  hipStream_t first = nullptr;
+  {
+    ServiceStream a, b;
+    check(a.st && b.st && a.st != b.st, "one stream for two calls");
+    first = b.st;  // given back first
+  }
+  {
+    ServiceStream a;
+    check(a.st != nullptr, "no stream");
+    a.broken = true;
+    first = a.st;
+  }
+  {
+    ServiceStream a, b;
+    check(a.st != first && b.st != first, "a broken stream was kept");
+  }
+  std::mutex m;
+  std::set<hipStream_t> busy;
+  std::vector<std::thread> ts;
+  for (int t = 0; t < 8; ++t)
+    ts.emplace_back([&] {
+      for (int k = 0; k < 500; ++k) {
+        ServiceStream a;
+        {
+          std::lock_guard<std::mutex> g(m);
+          check(busy.insert(a.st).second, "one stream for two calls");
+        }
+        std::this_thread::yield();
+        std::lock_guard<std::mutex> g(m);
+        busy.erase(a.st);
+      }
+    });
+  for (std::thread& t : ts) t.join();
+  check(g_streams_made.size() <= 4, "idle streams without bound");
+  pool_trim();
+  check(g_streams_made.empty(), "streams left after the trim");
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const char* name = argc > 1 ? argv[1] : "";
   if (!strcmp(name, "release_beside_grow")) release_beside_grow();
   else if (!strcmp(name, "many_threads")) many_threads();
+  else if (!strcmp(name, "service_streams")) service_streams();
   else if (!strcmp(name, "scope_under_pressure")) scope_under_pressure();
   else if (!strcmp(name, "release_beside_capture")) release_beside_capture();
   else fail("no such scenario");

@@ -39,3 +39,7 @@ def test_releases_wait_and_leave_captures_of_other_threads_alone(shim):
 
 def test_released_buffers_of_a_scope_are_bounded_and_given_back(shim):
     shim("scope_under_pressure")
+
+
+def test_streams_pass_between_calls(shim):
+    shim("service_streams")
