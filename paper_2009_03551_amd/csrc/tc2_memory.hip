@@ -222,7 +222,7 @@ void pool_trim() {
     for (auto& r : P->ranges) {
       (void)hipMemUnmap(r.first, P->chunk);
       (void)hipMemAddressFree(r.first, P->va);
-      P->free.push_back(r.second);
+      (void)hipMemRelease(r.second);
     }
     P->ranges.clear();
     for (hipMemGenericAllocationHandle_t h : P->free) (void)hipMemRelease(h);

@@ -14,6 +14,16 @@
 #include <set>
 #include <thread>
 
+// host memory that has run out for this thread
+static thread_local bool g_no_host_memory = false;
+void* operator new(size_t n) {
+  void* p = g_no_host_memory ? nullptr : malloc(n ? n : 1);
+  if (!p) throw std::bad_alloc();
+  return p;
+}
+void operator delete(void* p) noexcept { free(p); }
+void operator delete(void* p, size_t) noexcept { free(p); }
+
 namespace {
 
 constexpr size_t MB = (size_t)1 << 20, GB = (size_t)1 << 30;
@@ -330,12 +340,35 @@ void service_streams() {
   check(g_streams_made.empty(), "streams left after the trim");
 }
 
+// tc2_trim_memory has no way to report an exception: without host memory the
+// pool still goes back to the driver.
+void trim_without_host_memory() {
+  {
+    DBuf b[6];
+    for (DBuf& x : b) check(x.reserve(300 * MB) == hipSuccess && x.chunks.size() == 2, "reserve");
+    void* p = nullptr;
+    check(dev_malloc(&p, 3 * MB) == hipSuccess, "small buffer");
+    dev_free(p);
+  }
+  // as many free chunks as their list has room for
+  DBuf first;
+  std::vector<hipMemGenericAllocationHandle_t>& list = g_pool[0].free;
+  check(first.reserve(200 * MB) == hipSuccess, "reserve");
+  first.release();
+  list.shrink_to_fit();
+  g_no_host_memory = true;
+  pool_trim();
+  g_no_host_memory = false;
+  check(g_in_use == 0 && g_mapped.empty() && g_reserved.empty(), "memory left after the trim");
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const char* name = argc > 1 ? argv[1] : "";
   if (!strcmp(name, "release_beside_grow")) release_beside_grow();
   else if (!strcmp(name, "many_threads")) many_threads();
+  else if (!strcmp(name, "trim_without_host_memory")) trim_without_host_memory();
   else if (!strcmp(name, "service_streams")) service_streams();
   else if (!strcmp(name, "scope_under_pressure")) scope_under_pressure();
   else if (!strcmp(name, "release_beside_capture")) release_beside_capture();

@@ -43,3 +43,7 @@ def test_released_buffers_of_a_scope_are_bounded_and_given_back(shim):
 
 def test_streams_pass_between_calls(shim):
     shim("service_streams")
+
+
+def test_trim_without_host_memory(shim):
+    shim("trim_without_host_memory")
