@@ -600,8 +600,10 @@ tc2_status tc2_setup(const tc2_problem* problems, int32_t n_problems, const tc2_
 // ====================================================================== solve
 namespace {
 
-// Copy the current iterate into fresh buffers of another precision.
+// Copy the current iterate into fresh buffers of another precision.  A solve that
+// ends within its leading FP64 updates is in FP64 when its closing pair is due.
 tc2_status convert_iterate(tc2_ctx* ctx, hipStream_t st, int to_prec) {
+  if (ctx->cur_prec == to_prec) return TC2_OK;
   ctx->bn_valid = false;  // the norms of the converted values are taken anew
   int c = ctx->cur;
   long long n = (long long)ctx->nnz[c] * (1 + ctx->D) * BS;

@@ -184,3 +184,31 @@ def test_trace_groups_of_whole_subtiles(knob, kind, D):
     assert c.alpha == pytest.approx(b.alpha, rel=1e-12)
     for x, y in zip([c.X0] + c.X1, [b.X0] + b.X1):
         assert np.array_equal(x.val, y.val)
+
+
+@pytest.mark.parametrize("graph", [False, True])
+@pytest.mark.parametrize("kind", ["fp32", "bf16", "fp32w", "bf16w"])
+def test_reduced_solve_that_ends_in_its_leading_fp64_updates(kind, graph):
+    # the closing pair then starts from an FP64 iterate: two more FP64 updates of
+    # the converged X0, and systems without or with all states occupied unchanged
+    opts = dict(KINDS[kind], fp64_first=60, skip="bound", graph=graph)
+    s = W.batch_systems(sizes=[29, 12, 17], n_dir=2, b=6)
+    s[1].n_occ, s[2].n_occ = 0, s[2].H.n
+    ref = T.solve(s, skip="bound")
+    for trivial in (False, True):
+        got = T.solve(s[1:] if trivial else s, **opts)
+        for a, b in zip(got, ref[1:] if trivial else ref):
+            assert a.status_name == b.status_name
+            for x, y in zip([a.X0] + a.X1, [b.X0] + b.X1):
+                if a is got[0] and not trivial:
+                    d = np.abs(dense(x) - dense(y)).max()
+                    assert d < 1e-5, d  # ten times the drop threshold
+                else:
+                    assert np.array_equal(x.row_ptr, y.row_ptr) and np.array_equal(x.col, y.col)
+                    assert np.array_equal(x.val, y.val)
+
+
+def dense(m):
+    A = np.zeros((m.nb, m.nb, m.b, m.b))
+    A[np.repeat(np.arange(m.nb), np.diff(m.row_ptr)), m.col] = m.val
+    return A
