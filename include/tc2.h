@@ -270,8 +270,9 @@ typedef struct {
  * progress begins first (Gershgorin bounds and the initial matrices, as
  * tc2_run).  When a solve finishes within the call (every system stopped and
  * no stage switch pending), its results are written to res (n_problems
- * entries, as tc2_run) and, if updates remain, the next solve begins from H.
- * The updates and results are those of tc2_run: a solve advanced in pieces
+ * entries, as tc2_run) and, if updates remain, the next solve begins from H
+ * (not when a solve has no update to run: no, or every, state occupied in all
+ * systems; the call then returns after one).  The updates and results are those of tc2_run: a solve advanced in pieces
  * gives the same iterates.  tc2_run abandons a solve in progress.
  * Returns the worst status of the solves finished in this call (TC2_OK if
  * none finished), or an error; prog is filled in either case.

@@ -2267,9 +2267,11 @@ tc2_status advance_impl(tc2_ctx* ctx, void* stream, int32_t max_updates, tc2_pro
     }
     if (done) {
       if ((r = bank()) != TC2_OK) return r;
+      const bool none = R.updates == 0;  // every system trivial: no update to run
       worst = finish_solve(ctx, res);
       if (worst < 0) return worst;
       prog->solves_completed++;
+      if (none) break;
       continue;
     }
     prog->updates++;

@@ -212,3 +212,19 @@ def dense(m):
     A = np.zeros((m.nb, m.nb, m.b, m.b))
     A[np.repeat(np.arange(m.nb), np.diff(m.row_ptr)), m.col] = m.val
     return A
+
+
+@pytest.mark.parametrize("opts", [dict(), dict(FP32, fp64_first=2)])
+def test_advance_of_systems_without_an_update(opts):
+    # no state, or every state, occupied: a solve has no update to run, and a call
+    # returns after one such solve
+    s = W.batch_systems(sizes=[9, 17], n_dir=1, b=5)
+    s[0].n_occ, s[1].n_occ = 0, s[1].H.n
+    ref = T.solve(s, **opts)
+    sv = T.Solver(s, **opts)
+    for _ in range(2):
+        p, r = sv.advance(5)
+        assert p["updates"] == 0 and p["solves_completed"] == 1 and not p["solve_open"]
+        for a, b in zip(r, ref):
+            same(a, b)
+    sv.close()
