@@ -30,19 +30,6 @@ void vm_release(DBuf& b);                  // chunks back to the pool, range fre
 void pool_trim();                          // pooled chunks of the device to the GPU driver
 bool device_wait();                        // for all work of the device; captures go on
 
-// A stream of the current device for the copies of a set-up or one graph capture,
-// kept for the next one afterwards (broken: not kept); st is null when none can
-// be made.  The work on it has ended when it is given back.
-struct ServiceStream {
-  hipStream_t st = nullptr;
-  int dev = 0;
-  bool broken = false;
-  ServiceStream();
-  ~ServiceStream();
-  ServiceStream(const ServiceStream&) = delete;
-  ServiceStream& operator=(const ServiceStream&) = delete;
-};
-
 struct DBuf {
   void* p = nullptr;
   size_t cap = 0;

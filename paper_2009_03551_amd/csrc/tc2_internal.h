@@ -280,6 +280,20 @@ struct MemScope {
   bool drain();
 };
 
+// A stream of the current device for a call of the skip network, the copies of a
+// set-up or one graph capture, kept for the next one afterwards (broken: not
+// kept); st is null when none can be made.  The work on it has ended when it is
+// given back.
+struct ServiceStream {
+  hipStream_t st = nullptr;
+  int dev = 0;
+  bool broken = false;
+  ServiceStream();
+  ~ServiceStream();
+  ServiceStream(const ServiceStream&) = delete;
+  ServiceStream& operator=(const ServiceStream&) = delete;
+};
+
 // kernels (launch wrappers), all asynchronous on `st`
 void launch_gershgorin(hipStream_t st, int nb, int b, const int* rp, const int* ci,
                        const double* hv, double* rowlo, double* rowhi);

@@ -395,10 +395,6 @@ struct DevMem {
     if (e_ != hipSuccess) return e_ == hipErrorOutOfMemory ? TC2_ENOMEM : TC2_EDEVICE; \
   } while (0)
 
-// Stream of the entry points with host arrays: the thread's own, as a copy on the
-// null stream would disturb a graph capture of another thread.
-#define MLP_ST hipStreamPerThread
-
 tc2_status use_device(int device) {
   int ndev = 0;
   if (hipGetDeviceCount(&ndev) != hipSuccess || ndev < 1) return TC2_EDEVICE;
@@ -471,16 +467,20 @@ tc2_status tc2_mlp_forward(const float* theta, const float* x, int64_t n, int32_
   tc2_status s = use_device(device);
   if (s != TC2_OK) return s;
   if (n == 0) return TC2_OK;
+  const ServiceStream svc;
+  if (!svc.st) return TC2_EDEVICE;
+  MemScope scope;  // waits for the stream at the end of the call
+  scope.open(svc.st);
   DevMem dth, dx, dout;
   MLPCHK(dth.alloc(MLP_NP * 4));
   MLPCHK(dx.alloc((size_t)n * MLP_NF * 4));
   MLPCHK(dout.alloc((size_t)n * 4));
-  MLPCHK(hipMemcpyWithStream(dth.p, theta, MLP_NP * 4, hipMemcpyHostToDevice, MLP_ST));
-  MLPCHK(hipMemcpyWithStream(dx.p, x, (size_t)n * MLP_NF * 4, hipMemcpyHostToDevice, MLP_ST));
-  hipLaunchKernelGGL(k_mlp_forward, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, MLP_ST,
+  MLPCHK(hipMemcpyAsync(dth.p, theta, MLP_NP * 4, hipMemcpyHostToDevice, svc.st));
+  MLPCHK(hipMemcpyAsync(dx.p, x, (size_t)n * MLP_NF * 4, hipMemcpyHostToDevice, svc.st));
+  hipLaunchKernelGGL(k_mlp_forward, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, svc.st,
                      dth.as<float>(), dx.as<float>(), (long long)n, dout.as<float>());
   MLPCHK(hipGetLastError());
-  MLPCHK(hipMemcpyWithStream(logits, dout.p, (size_t)n * 4, hipMemcpyDeviceToHost, MLP_ST));
+  MLPCHK(hipMemcpyWithStream(logits, dout.p, (size_t)n * 4, hipMemcpyDeviceToHost, svc.st));
   return TC2_OK;
 }
 
@@ -507,19 +507,23 @@ tc2_status tc2_mlp_grad(const float* theta, const float* x, const float* y, int6
                at_y = place((size_t)n * 4), at_g = place((size_t)nblk * MLP_NP * 4),
                at_l = place((size_t)nblk * 8), at_b = place((size_t)nblk * 4),
                at_r = place(sizeof(Result));
+  const ServiceStream svc;
+  if (!svc.st) return TC2_EDEVICE;
+  MemScope scope;  // waits for the stream at the end of the call
+  scope.open(svc.st);
   DevMem mem;
   MLPCHK(mem.alloc(size));
   char* base = mem.as<char>();
-  MLPCHK(hipMemcpyWithStream(base + at_th, theta, MLP_NP * 4, hipMemcpyHostToDevice, MLP_ST));
-  MLPCHK(hipMemcpyWithStream(base + at_x, x, (size_t)n * MLP_NF * 4, hipMemcpyHostToDevice, MLP_ST));
-  MLPCHK(hipMemcpyWithStream(base + at_y, y, (size_t)n * 4, hipMemcpyHostToDevice, MLP_ST));
+  MLPCHK(hipMemcpyAsync(base + at_th, theta, MLP_NP * 4, hipMemcpyHostToDevice, svc.st));
+  MLPCHK(hipMemcpyAsync(base + at_x, x, (size_t)n * MLP_NF * 4, hipMemcpyHostToDevice, svc.st));
+  MLPCHK(hipMemcpyAsync(base + at_y, y, (size_t)n * 4, hipMemcpyHostToDevice, svc.st));
   Result* dr = (Result*)(base + at_r);
-  if (tc2_status s = grad_dev(MLP_ST, (float*)(base + at_th), (float*)(base + at_x), (float*)(base + at_y), n,
+  if (tc2_status s = grad_dev(svc.st, (float*)(base + at_th), (float*)(base + at_x), (float*)(base + at_y), n,
                               (float*)(base + at_g), (double*)(base + at_l), dr->grad, &dr->loss,
                               (int*)(base + at_b), &dr->bad);
       s != TC2_OK)
     return s;
-  MLPCHK(hipMemcpyWithStream(&res, dr, sizeof(Result), hipMemcpyDeviceToHost, MLP_ST));
+  MLPCHK(hipMemcpyWithStream(&res, dr, sizeof(Result), hipMemcpyDeviceToHost, svc.st));
   if (res.bad) return TC2_ENAN;
   memcpy(grad, res.grad, sizeof(res.grad));
   *loss = res.loss;
@@ -537,6 +541,10 @@ tc2_status tc2_mlp_train(const float* x, const float* y, int64_t n, const tc2_ml
   if (s != TC2_OK) return s;
   const long long B = std::min<long long>(o->batch, n);
   const int nblk = (int)((B + GS - 1) / GS);
+  const ServiceStream svc;
+  if (!svc.st) return TC2_EDEVICE;
+  MemScope scope;  // waits for the stream at the end of the call
+  scope.open(svc.st);
   DevMem dth, dm, dv, dx, dy, gpart, lpart, dg, dl;
   MLPCHK(dth.alloc(MLP_NP * 4));
   MLPCHK(dm.alloc(MLP_NP * 4));
@@ -547,31 +555,31 @@ tc2_status tc2_mlp_train(const float* x, const float* y, int64_t n, const tc2_ml
   MLPCHK(lpart.alloc((size_t)nblk * 8));
   MLPCHK(dg.alloc(MLP_NP * 4));
   MLPCHK(dl.alloc(8));
-  MLPCHK(hipMemcpyWithStream(dth.p, theta, MLP_NP * 4, hipMemcpyHostToDevice, MLP_ST));
-  MLPCHK(hipMemsetAsync(dm.p, 0, MLP_NP * 4, MLP_ST));
-  MLPCHK(hipMemsetAsync(dv.p, 0, MLP_NP * 4, MLP_ST));
-  MLPCHK(hipMemcpyWithStream(dx.p, x, (size_t)n * MLP_NF * 4, hipMemcpyHostToDevice, MLP_ST));
-  MLPCHK(hipMemcpyWithStream(dy.p, y, (size_t)n * 4, hipMemcpyHostToDevice, MLP_ST));
+  MLPCHK(hipMemcpyAsync(dth.p, theta, MLP_NP * 4, hipMemcpyHostToDevice, svc.st));
+  MLPCHK(hipMemsetAsync(dm.p, 0, MLP_NP * 4, svc.st));
+  MLPCHK(hipMemsetAsync(dv.p, 0, MLP_NP * 4, svc.st));
+  MLPCHK(hipMemcpyAsync(dx.p, x, (size_t)n * MLP_NF * 4, hipMemcpyHostToDevice, svc.st));
+  MLPCHK(hipMemcpyAsync(dy.p, y, (size_t)n * 4, hipMemcpyHostToDevice, svc.st));
   int t = 0;
   for (int ep = 0; ep < o->epochs; ++ep) {
     double ep_loss = 0.0;
     for (long long b0 = 0; b0 < n; b0 += B) {
       const long long nb = std::min<long long>(B, n - b0);
-      s = grad_dev(MLP_ST, dth.as<float>(), dx.as<float>() + b0 * MLP_NF, dy.as<float>() + b0, nb,
+      s = grad_dev(svc.st, dth.as<float>(), dx.as<float>() + b0 * MLP_NF, dy.as<float>() + b0, nb,
                    gpart.as<float>(), lpart.as<double>(), dg.as<float>(), dl.as<double>());
       if (s != TC2_OK) return s;
       ++t;
-      hipLaunchKernelGGL(k_adam, dim3((MLP_NP + 255) / 256), dim3(256), 0, MLP_ST, dth.as<float>(),
+      hipLaunchKernelGGL(k_adam, dim3((MLP_NP + 255) / 256), dim3(256), 0, svc.st, dth.as<float>(),
                          dm.as<float>(), dv.as<float>(), dg.as<float>(), o->lr, o->beta1, o->beta2,
                          o->adam_eps, t);
       MLPCHK(hipGetLastError());
       double bl = 0.0;
-      MLPCHK(hipMemcpyWithStream(&bl, dl.p, 8, hipMemcpyDeviceToHost, MLP_ST));
+      MLPCHK(hipMemcpyWithStream(&bl, dl.p, 8, hipMemcpyDeviceToHost, svc.st));
       ep_loss += bl * (double)nb / (double)n;
     }
     if (loss_per_epoch) loss_per_epoch[ep] = ep_loss;
   }
-  MLPCHK(hipMemcpyWithStream(theta, dth.p, MLP_NP * 4, hipMemcpyDeviceToHost, MLP_ST));
+  MLPCHK(hipMemcpyWithStream(theta, dth.p, MLP_NP * 4, hipMemcpyDeviceToHost, svc.st));
   return TC2_OK;
 }
 

@@ -79,11 +79,12 @@ void pack_blocks(const tc2_bsr& m, int b, std::vector<double>& out) {
         out[off + (size_t)e * BS + c * BP + r] = m.val[(e * b + r) * b + c];
 }
 
+// h stays as it is until the next wait for ctx->up
 template <typename T>
 tc2_status upload(tc2_ctx* ctx, DBuf& d, const std::vector<T>& h) {
   HIPCHK(d.reserve(h.size() * sizeof(T)));
   if (!h.empty())
-    HIPCHK(hipMemcpyWithStream(d.p, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice, ctx->up));
+    HIPCHK(hipMemcpyAsync(d.p, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice, ctx->up));
   return TC2_OK;
 }
 
@@ -381,6 +382,7 @@ static tc2_status setup_impl(const tc2_problem* probs, int32_t np, const tc2_opt
   const ServiceStream up;
   if (!up.st) return fail(TC2_EDEVICE);
   ctx->up = up.st;
+  auto uploaded = [&] { return hipStreamSynchronize(up.st) == hipSuccess; };
   if (ctx->profile)
     for (hipEvent_t& e : ctx->pev)
       if (hipEventCreate(&e) != hipSuccess) return fail(TC2_EDEVICE);
@@ -437,6 +439,7 @@ static tc2_status setup_impl(const tc2_problem* probs, int32_t np, const tc2_opt
   for (int d = 0; d < D; ++d) {
     std::vector<const tc2_bsr*> m1(np);
     for (int s = 0; s < np; ++s) m1[s] = &probs[s].H1[d];
+    if (!uploaded()) return fail(TC2_EDEVICE);
     vals.clear();
     merge_pattern(m1, ctx->sys, h1rp[d], h1ci[d]);
     for (int s = 0; s < np; ++s) pack_blocks(probs[s].H1[d], b, vals);
@@ -552,6 +555,7 @@ static tc2_status setup_impl(const tc2_problem* probs, int32_t np, const tc2_opt
     if ((st = upload(ctx, ctx->atom_clus, atom_clus)) != TC2_OK) return fail(st);
     if ((st = upload(ctx, ctx->csys_start, csys_start)) != TC2_OK) return fail(st);
     if ((st = upload(ctx, ctx->csys_end, csys_end)) != TC2_OK) return fail(st);
+    if (!uploaded()) return fail(TC2_EDEVICE);
   }
   // positions (a feature of the skip network) and the network itself
   {
@@ -561,12 +565,14 @@ static tc2_status setup_impl(const tc2_problem* probs, int32_t np, const tc2_opt
       std::vector<double> xyz;
       for (int s = 0; s < np; ++s) xyz.insert(xyz.end(), probs[s].xyz, probs[s].xyz + 3 * (size_t)probs[s].H.nb);
       if ((st = upload(ctx, ctx->xyz, xyz)) != TC2_OK) return fail(st);
+      if (!uploaded()) return fail(TC2_EDEVICE);
       ctx->have_xyz = true;
     }
     if (o->skip == 2) {
       if (ctx->mlp_bsum.reserve((size_t)np * 8) != hipSuccess) return fail(TC2_ENOMEM);
       std::vector<float> th(o->mlp_weights, o->mlp_weights + MLP_NP);
       if ((st = upload(ctx, ctx->mlp, th)) != TC2_OK) return fail(st);
+      if (!uploaded()) return fail(TC2_EDEVICE);
       ctx->mlp_z = std::log(o->mlp_threshold / (1.f - o->mlp_threshold));
     }
     if (ctx->log_cap > 0) {
@@ -578,7 +584,7 @@ static tc2_status setup_impl(const tc2_problem* probs, int32_t np, const tc2_opt
   }
   if (ctx->rowlo.reserve((size_t)ctx->nb * b * 8) || ctx->rowhi.reserve((size_t)ctx->nb * b * 8))
     return fail(TC2_ENOMEM);
-  if (hipStreamSynchronize(up.st) != hipSuccess) return fail(TC2_EDEVICE);
+  if (!uploaded()) return fail(TC2_EDEVICE);
   ctx->up = nullptr;
   *out = ctx;
   return TC2_OK;
